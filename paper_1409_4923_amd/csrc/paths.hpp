@@ -76,60 +76,57 @@ template <int POT> __device__ __forceinline__ float force_plus(float x, float A,
     }
 }
 
-// cos y in FP64.  Cody-Waite reduction y = k pi/2 + r, k = rint(2y/pi), with pi/2
-// split into three doubles (the first two of 33 significant bits, so k times each is
-// exact for |k| < 2^20), r in [-pi/4, pi/4]; then the Taylor series of sin r to r^17
-// and of cos r to r^16 (remainders below 1e-19 and 3e-18 on that interval), and k
-// mod 4 picks cos r, -sin r, -cos r or sin r.  A lane whose argument has |y| >= 2^20
-// (or is NaN) takes the library cos instead; the other lanes keep the polynomial, so
-// a path's value never depends on the paths that share its wave.
-__device__ __noinline__ double cos_library(double y) { return cos(y); }
+// cos 2 pi x and the sine potential's force in FP64, with the argument in turns:
+// r = x - rint(x) is exact for every finite x and cos 2 pi x = sin 2 pi s with
+// s = 1/4 - |r| in [-1/4, 1/4], so one odd polynomial serves every x -- no reduction by
+// pi/2, no second polynomial, no quadrant and no fallback for large arguments.
+// sin 2 pi s = s (c0 + z Q(z)), z = s^2, the c_k a relative minimax fit on z <= 1/16
+// (Remez exchange in 60 digits: 2.6e-19) rounded to nearest, c0 in two doubles.  The
+// value lies within 1.1e-16 of cos 2 pi x, where the cosine of the rounded argument
+// 2 pi x is up to 4.4e-16 away.
+// FP64 VALU issue bounds the FP64 kernels (4.3 cycles per wave instruction and SIMD, and
+// nothing issues beside it): 13 - 14 instructions per evaluation, where two polynomials
+// behind a three-part reduction by pi/2 took about 45.  Inertial Poisson model, 262147 FP64 paths
+// x 800 steps: 612 us a call, 1400 us before; 1024 paths x 600 steps (the latency of one
+// wave's chain): 117 us, 300 us before.
+__device__ __forceinline__ double turn_quarter(double x) { return 0.25 - fabs(x - rint(x)); }
 
-__device__ __forceinline__ double cos_fp64(double y_in)
+constexpr double SIN_C0 = 0x1.921fb54442d18p+2, SIN_C0_LO = 0x1.1a62633145c07p-52;
+constexpr double SIN_C[8] = {-0x1.4abbce625be52p+5, 0x1.466bc6775aa6ep+6,  -0x1.32d2cce627542p+6,
+                             0x1.50783485190c5p+5,  -0x1.e3074ddd1d40dp+3, 0x1.e8f35e9d4c4a0p+1,
+                             -0x1.6f79770a5bb06p-1, 0x1.9d1b8657cb612p-4};
+
+__device__ __forceinline__ double cos_turns(double x)
 {
-    const bool big = !(fabs(y_in) < 0x1p20);
-    double lib = 0.0;
-    if (__builtin_amdgcn_ballot_w64(big) != 0) {
-        if (big) lib = cos_library(y_in);
-    }
-    const double y = big ? 0.0 : y_in;                               // keeps the reduction exact
-    const double k = rint(y * 0x1.45f306dc9c883p-1);                 // 2/pi
-    double r = fma(-k, 0x1.921fb544p+0, y);                          // pi/2, first 33 bits
-    r = fma(-k, 0x1.0b4611a6p-34, r);                                //       next 33 bits
-    r = fma(-k, 0x1.3198a2e037073p-69, r);                           //       the rest
-    const double r2 = r * r;
-    // coefficients (-1)^j / n!, n = 2j + 1 (sin) or 2j (cos), rounded to nearest
-    double ps = 0x1.952c77030ad4ap-49;                               //  1/17!
-    ps = fma(ps, r2, -0x1.ae7f3e733b81fp-41);                        // -1/15!
-    ps = fma(ps, r2, 0x1.6124613a86d09p-33);                         //  1/13!
-    ps = fma(ps, r2, -0x1.ae64567f544e4p-26);                        // -1/11!
-    ps = fma(ps, r2, 0x1.71de3a556c734p-19);                         //  1/9!
-    ps = fma(ps, r2, -0x1.a01a01a01a01ap-13);                        // -1/7!
-    ps = fma(ps, r2, 0x1.1111111111111p-7);                          //  1/5!
-    ps = fma(ps, r2, -0x1.5555555555555p-3);                         // -1/3!
-    const double sn = fma(r * r2, ps, r);
-    double pc = 0x1.ae7f3e733b81fp-45;                               //  1/16!
-    pc = fma(pc, r2, -0x1.93974a8c07c9dp-37);                        // -1/14!
-    pc = fma(pc, r2, 0x1.1eed8eff8d898p-29);                         //  1/12!
-    pc = fma(pc, r2, -0x1.27e4fb7789f5cp-22);                        // -1/10!
-    pc = fma(pc, r2, 0x1.a01a01a01a01ap-16);                         //  1/8!
-    pc = fma(pc, r2, -0x1.6c16c16c16c17p-10);                        // -1/6!
-    pc = fma(pc, r2, 0x1.5555555555555p-5);                          //  1/4!
-    pc = fma(pc, r2, -0.5);                                          // -1/2!
-    const double cs = fma(r2, pc, 1.0);
-    const int q = (int)k & 3;                                        // k mod 4 (two's complement)
-    const double v = (q & 1) ? sn : cs;
-    const double poly = (q == 1 || q == 2) ? -v : v;
-    return big ? lib : poly;
+    const double s = turn_quarter(x), z = s * s;
+    double q = SIN_C[7];
+#pragma unroll
+    for (int k = 6; k >= 0; --k) q = fma(q, z, SIN_C[k]);
+    return fma(s, SIN_C0, s * fma(z, q, SIN_C0_LO));
+}
+
+// A - 2 pi cos 2 pi x: the same polynomial times -2 pi, its last multiplication merged
+// with the addition of A.
+constexpr double FORCE_C0 = -0x1.3bd3cc9be45dep+5, FORCE_C0_LO = -0x1.692b71366cc04p-49;
+constexpr double FORCE_C[8] = {0x1.03c1f081b5ac3p+8, -0x1.005ed5ead8fa0p+9, 0x1.e1f5068914938p+8,
+                               -0x1.084337a3092afp+8, 0x1.7b5ea6164de3cp+6, -0x1.80055d20f480dp+4,
+                               0x1.209d206b45ca0p+2, -0x1.447431e6df8f9p-1};
+
+__device__ __forceinline__ double sine_force_plus(double x, double A)
+{
+    const double s = turn_quarter(x), z = s * s;
+    double q = FORCE_C[7];
+#pragma unroll
+    for (int k = 6; k >= 0; --k) q = fma(q, z, FORCE_C[k]);
+    return fma(s, FORCE_C0, fma(s, fma(z, q, FORCE_C0_LO), A));
 }
 
 template <int POT> __device__ __forceinline__ double force_plus(double x, double A, double kp)
 {
-    constexpr double PI = 3.14159265358979323846;
     if constexpr (POT == POT_SIN) {
-        return fma(kp, cos_fp64(2.0 * PI * x), A);
+        return sine_force_plus(x, A);
     } else if constexpr (POT == POT_RATCHET) {
-        const double c = cos_fp64(2.0 * PI * x);
+        const double c = cos_turns(x);
         return fma(c, fma(kp, c, kp), A);                                 // A includes -pi
     } else if constexpr (POT == POT_TENT) {
         const double y = x - 2.0 * floor(x / 2.0);

@@ -210,10 +210,12 @@ template <typename R> struct JGKick {
     R th, z, u;
 };
 constexpr uint32_t JG_NONE = 0xFFFFFFFFu;
-// Queued kicks per lane and window of the jump-adapted grid (more are drawn at their
-// steps): 10 in FP32, 6 in FP64, so that the FP64 queues of 256 lanes with the
-// dichotomous queue still fit in 64 KiB of LDS.
-template <typename R> constexpr uint32_t jg_cap() { return sizeof(R) == 4 ? 10u : 6u; }
+// Queued kicks per lane and window of the jump-adapted grid (more wait for the next
+// window): 9 in FP32, so that four groups of 256 lanes with their increment tables fit a
+// CU's 160 KiB (10 leave room for three: 3.82 against 3.60 ms per 500001 paths x 4000
+// steps); 6 in FP64, so that the FP64 queues of 256 lanes with the dichotomous queue
+// still fit in 64 KiB of LDS.
+template <typename R> constexpr uint32_t jg_cap() { return sizeof(R) == 4 ? 9u : 6u; }
 
 template <typename R> struct KickEntry {
     uint32_t off;   // step offset in the window (>= the steps run: none left)

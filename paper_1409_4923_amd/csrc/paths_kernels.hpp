@@ -362,6 +362,40 @@ __device__ __forceinline__ void full_step(const PointConst &a, uint32_t path, Pa
 }
 
 
+// Three-point increments from a table of digit pairs in LDS, one table per wave (the
+// waves of a scan hold different points): entry 6 a + b is the pair (increment of digit
+// a, increment of digit b).  The step loop is bound by VALU issue, and compares, selects
+// and shifts take the same issue slot as an FMA (4.2 - 4.9 cycles per wave instruction and
+// SIMD) while adds and logic issue beside one (2.6): two compares, two selects and a
+// multiplication by 6 per step were 20 of its 112 cycles (inertial Poisson, FP32).  The
+// pair costs a multiply and a mask, once per two steps.  2^20 paths x 4000 steps: 3.10 ->
+// 2.81 ms (inertial Poisson), 2.84 -> 2.64 ms (overdamped dichotomous).
+template <typename R> struct alignas(2 * sizeof(R)) Pair { R a, b; };
+template <typename R, int NOISE> constexpr uint32_t digit_bytes()
+{
+    return (NOISE & NZ_GAUSS) != 0 ? 36u * (uint32_t)sizeof(Pair<R>) : 0u;
+}
+// LDS bytes a work-group of `waves` waves needs for its tables (before the queues).
+template <typename R, int NOISE> __host__ __device__ constexpr uint32_t table_lds(uint32_t waves)
+{
+    return digit_bytes<R, NOISE>() * waves;
+}
+
+template <typename R> __device__ __forceinline__ R digit_increment(uint32_t digit, R g3)
+{
+    return digit == 0u ? -g3 : (digit == 1u ? g3 : R(0));
+}
+
+// Increments of the two leading base-6 digits of u, from the table at LDS offset `tab`
+// (a multiple of the entry size S): floor(36 u / 2^32) S = floor(36 S u / 2^32) with the
+// low bits cleared, so one multiply and one mask give the address.
+template <typename R> __device__ __forceinline__ Pair<R> digit_pair(const unsigned char *smem, uint32_t tab, uint32_t u)
+{
+    constexpr uint32_t S = (uint32_t)sizeof(Pair<R>);
+    const uint32_t off = (uint32_t)(((uint64_t)u * (36u * S) + ((uint64_t)tab << 32)) >> 32) & ~(S - 1u);
+    return *reinterpret_cast<const Pair<R> *>(smem + off);
+}
+
 // LDS bytes of the jump queues per lane and path.
 template <typename R, int NOISE> constexpr uint32_t queue_bytes()
 {
@@ -383,8 +417,18 @@ template <typename R, int NOISE> constexpr uint32_t queue_bytes()
 template <typename R, int DYN, int POT, int NOISE, int PPL>
 __device__ __forceinline__ void advance_range(const PointConst &a, const uint32_t (&path)[PPL],
                                               Path<R> (&s)[PPL], uint64_t n0, uint64_t n1,
-                                              unsigned char *smem, uint32_t qs, uint32_t col0)
+                                              unsigned char *lds, uint32_t qs, uint32_t col0)
 {
+    const uint32_t dtab = digit_bytes<R, NOISE>() * (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    unsigned char *smem = lds + table_lds<R, NOISE>(blockDim.x >> 6);
+    if constexpr ((NOISE & NZ_GAUSS) != 0) {
+        const uint32_t e = threadIdx.x & 63u;
+        if (e < 36u)
+            reinterpret_cast<Pair<R> *>(lds + dtab)[e] =
+                Pair<R>{digit_increment<R>(e / 6u, (R)a.g3), digit_increment<R>(e % 6u, (R)a.g3)};
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
     KickEntry<R> *kq = reinterpret_cast<KickEntry<R> *>(smem);
     JGKick<R> *gq = reinterpret_cast<JGKick<R> *>(smem);       // jump-adapted grid (no fixed-grid queue)
     uint32_t *fq = reinterpret_cast<uint32_t *>(
@@ -543,16 +587,25 @@ __device__ __forceinline__ void advance_range(const PointConst &a, const uint32_
                         normal_pair(qn.z, qn.w, zn[j][2], zn[j][3]);
                     }
                 }
+                R dx[PPL][4];                         // three-point increments of the same steps
+                if constexpr ((NOISE & NZ_GAUSS) != 0) {
+#pragma unroll
+                    for (int j = 0; j < PPL; ++j) {
+                        const Pair<R> p0 = digit_pair<R>(lds, dtab, u[j]);
+                        const Pair<R> p1 = digit_pair<R>(lds, dtab, 36u * u[j]);
+                        dx[j][0] = p0.a;
+                        dx[j][1] = p0.b;
+                        dx[j][2] = p1.a;
+                        dx[j][3] = p1.b;
+                    }
+                }
 #pragma unroll
                 for (int dg = 0; dg < 4; ++dg) {
                     const R A0 = A[4 * wd + dg], A1 = A[4 * wd + dg + 1];
 #pragma unroll
                     for (int j = 0; j < PPL; ++j) {
                         R dxi = R(0);
-                        if constexpr ((NOISE & NZ_GAUSS) != 0) {
-                            dxi = three_point<R>(u[j], g3);
-                            u[j] = times6(u[j]);   // next base-6 digit
-                        }
+                        if constexpr ((NOISE & NZ_GAUSS) != 0) dxi = dx[j][dg];
                         if constexpr ((NOISE & NZ_NORMAL) != 0) dxi = g3 * zn[j][dg];
                         full_step<R, DYN, POT, NOISE>(a, path[j], s[j], J[j], gq + col(j),
                                                       fq + col(j), qs, wlen, off, k + (uint32_t)(4 * wd + dg), dxi, h, hh, ngam,
@@ -604,16 +657,17 @@ template <typename R, int DYN, int POT, int NOISE, int PPL>
 __global__ void __launch_bounds__(512) k_advance(const KArgs a)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    const uint32_t base = blockIdx.x * PPL * blockDim.x + threadIdx.x;
-    if (base >= a.p.n_paths) return;
+    const uint64_t base = (uint64_t)blockIdx.x * PPL * blockDim.x + threadIdx.x;
+    if ((base & ~(uint64_t)63) >= a.p.n_paths) return;     // the whole wave
     uint32_t path[PPL];
     bool valid[PPL];
     Path<R> s[PPL];
 #pragma unroll
     for (int j = 0; j < PPL; ++j) {
-        const uint64_t p = (uint64_t)base + (uint64_t)j * blockDim.x;
+        // lanes past the end shadow the last path: the wave's tables and votes take every lane
+        const uint64_t p = base + (uint64_t)j * blockDim.x;
         valid[j] = p < a.p.n_paths;
-        path[j] = valid[j] ? (uint32_t)p : base;
+        path[j] = valid[j] ? (uint32_t)p : a.p.n_paths - 1u;
         load_path<R, POT, NOISE>(a, path[j], s[j]);
     }
     advance_range<R, DYN, POT, NOISE, PPL>(a.p, path, s, a.n0, a.n1, smem, PPL * blockDim.x, threadIdx.x);

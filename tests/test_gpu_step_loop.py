@@ -1,0 +1,34 @@
+"""Edges of the step loop's per-wave LDS tables and jump queues: waves with few paths,
+horizons and cuts that are no multiple of a block of steps."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+from helpers import say
+from paper_1409_4923_amd import bmotor as B
+from paper_1409_4923_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+BASE = {"gauss": W.C2.with_(noise=W.GAUSS), "poisson": W.C2, "dich": W.C3,
+        "jump-grid": W.C2.with_(noise=W.GAUSS | W.POISSON | W.JUMP_GRID)}
+
+
+def final(w, cuts, tune=None):
+    e = B.Ensemble(*W.to_c(w), tune=tune)
+    for c in cuts:
+        e.integrate(c)
+    return e.read()
+
+
+@pytest.mark.parametrize("prec", [W.F32, W.F64], ids=["f32", "f64"])
+@pytest.mark.parametrize("model", sorted(BASE))
+@pytest.mark.parametrize("n", [1, 20, 35, 36, 37, 64 + 3])
+def test_few_paths_in_a_wave(model, prec, n):
+    """A path does not depend on how many lanes of its wave hold a path."""
+    w = BASE[model].with_(prec=prec, n_steps=77, n_window=19)
+    say("few paths", model, prec, n)
+    ref = final(w.with_(n_paths=192), [77])
+    got = final(w.with_(n_paths=n), [5, 16, 56])
+    for a, b in ((ref.x, got.x), (ref.v, got.v), (ref.noise, got.noise)):
+        assert np.array_equal(a.numpy()[:n], b.numpy())

@@ -11,6 +11,7 @@
 #include "common.hpp"
 #include "host.hpp"
 #include "mlp_kernels.hpp"
+#include "mlp_train.hpp"
 
 using namespace bm;
 using namespace bm::host;
@@ -22,172 +23,6 @@ static_assert(IN == BM_MLP_INPUTS && H == BM_MLP_HIDDEN, "shape differs from bmo
 
 namespace {
 
-
-// ---------------------------------------------------------------------------
-// Small layers
-// ---------------------------------------------------------------------------
-// Layer 1 (5 -> 256) + GELU of the training forward; block = one row, lane = output;
-// grid (rows, members).  Row r of member m reads x[idx ? idx[m * idx_stride + r] : r].
-__global__ void __launch_bounds__(256) k_l1_fwd(const float *x, const uint32_t *idx, uint64_t idx_stride,
-                                                const bf16_t *wbf, const float *params, int rows, float *u_out,
-                                                float *z_out, bf16_t *a_out)
-{
-    const int r = blockIdx.x, m = blockIdx.y, o = threadIdx.x;
-    const uint64_t src = idx ? (uint64_t)idx[(uint64_t)m * idx_stride + r] : (uint64_t)r;
-    float u[IN];
-    normalise(x + src * IN, u);
-    const bf16_t *w = wbf + (uint64_t)m * NBF + BOFF_W1 + o * IN;
-    float z = params[(uint64_t)m * NPARAM + OFF_B1 + o];
-#pragma unroll
-    for (int j = 0; j < IN; ++j) z = fmaf(bf2f(w[j]), u[j], z);
-    const uint64_t row = (uint64_t)m * rows + r;
-    if (u_out && o < IN) u_out[row * IN + o] = u[o];
-    if (z_out) z_out[row * H + o] = z;
-    a_out[row * H + o] = f2bf(gelu(z));
-}
-
-// Output layer, loss and the output layer's gradients of the training step, fused.
-// Per row (one wave, four features per lane): y = a3 . W4 + b4, e = y - t,
-// dy = 2 e / B and dz3 = dy W4 gelu'(z3); per work-group of HEAD_ROWS rows the sums of
-// dy a3 (dW4), dy (db4) and e^2 (loss), combined over its waves in a fixed order.
-// grid (B / HEAD_ROWS, members), 256 lanes; B is a multiple of HEAD_ROWS.
-constexpr int HEAD_ROWS = 16;
-constexpr int HEAD_W = H + 2;          // partial record: dW4[256], db4, sum e^2
-
-__global__ void __launch_bounds__(256) k_head(const bf16_t *a3, const float *z3, const bf16_t *wbf,
-                                              const float *params, const float *t, const uint32_t *idx,
-                                              uint64_t idx_stride, int B, bf16_t *dz3, float *hpart)
-{
-    __shared__ float red[4][HEAD_W];
-    const int m = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const bf16_t *W4 = wbf + (uint64_t)m * NBF + BOFF_W4;
-    float w[4], sw[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-    for (int j = 0; j < 4; ++j) w[j] = bf2f(W4[lane * 4 + j]);
-    const float b4 = params[(uint64_t)m * NPARAM + OFF_B4];
-    float sb = 0.0f, se = 0.0f;
-#pragma unroll
-    for (int rr = 0; rr < HEAD_ROWS / 4; ++rr) {
-        const int r = blockIdx.x * HEAD_ROWS + wave * (HEAD_ROWS / 4) + rr;
-        const uint64_t row = (uint64_t)m * B + r;
-        float av[4];
-        float y = 0.0f;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            av[j] = bf2f(a3[row * H + lane * 4 + j]);
-            y = fmaf(av[j], w[j], y);
-        }
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) y += __shfl_xor(y, off, 64);   // the same sum in every lane
-        const uint64_t src = idx ? (uint64_t)idx[(uint64_t)m * idx_stride + r] : (uint64_t)r;
-        const float e = (y + b4) - t[src];
-        const float dy = 2.0f * e / (float)B;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            dz3[row * H + lane * 4 + j] = f2bf(dy * w[j] * gelu_grad(z3[row * H + lane * 4 + j]));
-            sw[j] = fmaf(dy, av[j], sw[j]);
-        }
-        sb += dy;
-        se = fmaf(e, e, se);
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) red[wave][lane * 4 + j] = sw[j];
-    if (lane == 0) {
-        red[wave][H] = sb;
-        red[wave][H + 1] = se;
-    }
-    __syncthreads();
-    float *out = hpart + ((uint64_t)m * gridDim.x + blockIdx.x) * HEAD_W;
-    for (int o = threadIdx.x; o < HEAD_W; o += 256) out[o] = ((red[0][o] + red[1][o]) + red[2][o]) + red[3][o];
-}
-
-// dW4, db4 and the loss of each member: the work-group partials added in order;
-// grid (members), 256 lanes.
-__global__ void __launch_bounds__(256) k_head_final(const float *hpart, int nblk, int B, float *grad, float *loss)
-{
-    const int m = blockIdx.x;
-    const float *p = hpart + (uint64_t)m * nblk * HEAD_W;
-    float *g = grad + (uint64_t)m * NPARAM;
-    for (int o = threadIdx.x; o < HEAD_W; o += 256) {
-        float s = 0.0f;
-#pragma unroll 8
-        for (int b = 0; b < nblk; ++b) s += p[(uint64_t)b * HEAD_W + o];
-        if (o < H) g[OFF_W4 + o] = s;
-        else if (o == H) g[OFF_B4] = s;
-        else if (loss) loss[m] = s / (float)B;
-    }
-}
-
-// Gradients that are column sums over the batch rather than GEMMs: the 5-wide input
-// layer (dW1[o][j] = sum_b dz1[b][o] u[b][j], db1 = sum_b dz1[b][:]).  (The biases of
-// the 256 x 256 layers come with their weight-gradient GEMM, the output layer with
-// k_head.)  Pass 1: grid
-// (n_chunks, members), lane = column o, each block sums one chunk of consecutive
-// rows; pass 2 adds the chunks in order, so the result does not depend on the launch.
-constexpr int RED_MAX_CHUNKS = 64;
-constexpr int NV1 = IN + 1;            // dW1[o][0..4], db1[o]
-
-__host__ __device__ inline int red_rows(int B) { return B / 64 < 16 ? 16 : B / 64; }
-
-__global__ void __launch_bounds__(256) k_colsum(const bf16_t *dz, const float *u, int B, int rows, float *part)
-{
-    const int c = blockIdx.x, m = blockIdx.y, o = threadIdx.x, nchunk = gridDim.x;
-    float s[NV1];
-#pragma unroll
-    for (int q = 0; q < NV1; ++q) s[q] = 0.0f;
-    const uint64_t row0 = (uint64_t)m * B + (uint64_t)c * rows;
-#pragma unroll 8
-    for (int r = 0; r < rows; ++r) {
-        const uint64_t row = row0 + r;
-        const float d = bf2f(dz[row * H + o]);
-#pragma unroll
-        for (int j = 0; j < IN; ++j) s[j] = fmaf(d, u[row * IN + j], s[j]);
-        s[IN] += d;
-    }
-#pragma unroll
-    for (int q = 0; q < NV1; ++q) part[(((uint64_t)m * nchunk + c) * NV1 + q) * H + o] = s[q];
-}
-
-// grid (NV1, members): block q adds the chunks of sum q (dW1[:][q], or db1 for q = IN).
-__global__ void __launch_bounds__(256) k_colsum_final(const float *part, int nchunk, float *grad)
-{
-    const int q = blockIdx.x, m = blockIdx.y, o = threadIdx.x;
-    float s = 0.0f;
-    // the chunks in order; unrolled so that the loads of several chunks are in flight
-#pragma unroll 8
-    for (int c = 0; c < nchunk; ++c) s += part[(((uint64_t)m * nchunk + c) * NV1 + q) * H + o];
-    float *g = grad + (uint64_t)m * NPARAM;
-    if (q < IN) g[OFF_W1 + o * IN + q] = s;
-    else g[OFF_B1 + o] = s;
-}
-
-hipError_t colsum(uint32_t nm, int B, const bf16_t *dz, const float *u, float *part, float *grad, hipStream_t s)
-{
-    const int rows = red_rows(B), nchunk = B / rows;
-    hipLaunchKernelGGL(k_colsum, dim3(nchunk, nm), dim3(256), 0, s, dz, u, B, rows, part);
-    hipLaunchKernelGGL(k_colsum_final, dim3(NV1, nm), dim3(256), 0, s, (const float *)part, nchunk, grad);
-    return hipGetLastError();
-}
-
-// Weight and bias gradients of a 256 x 256 layer from the ks split-K partials of
-// the weight-gradient GEMM, each element's partials added in order; grid
-// (H * H / 256 + 1, members): the last block of a member adds the bias partials.
-__global__ void __launch_bounds__(256) k_wgrad_sum(const float *wpart, const float *bpart, int ks, int nm,
-                                                   float *grad, int woff, int boff)
-{
-    const int m = blockIdx.y, t = threadIdx.x;
-    constexpr int NB = H * H / 256;
-    float *g = grad + (uint64_t)m * NPARAM;
-    float s = 0.0f;
-    if ((int)blockIdx.x < NB) {
-        const uint64_t e = (uint64_t)blockIdx.x * 256 + t;
-        for (int kc = 0; kc < ks; ++kc) s += wpart[((uint64_t)kc * nm + m) * (H * H) + e];
-        g[woff + e] = s;
-    } else {
-        for (int kc = 0; kc < ks; ++kc) s += bpart[((uint64_t)kc * nm + m) * H + t];
-        g[boff + t] = s;
-    }
-}
 
 // BF16 index of parameter p of a member, or -1 for biases.
 __device__ __forceinline__ int bf_index(int p)
@@ -311,17 +146,18 @@ __global__ void __launch_bounds__(256) k_compact(const float *stdv, uint64_t B, 
 size_t up(size_t v) { return (v + 255) & ~(size_t)255; }
 
 struct MlpLayout {
-    size_t u, z1, z2, z3, a1, a2, a3, y, dz1, dz2, dz3, hpart, red, wpart, bpart, blk, total;
+    size_t a1, a2, dz2, dz3, hpart, cpart, y, blk, total;
 };
 
-// Split of the batch (the K of the weight-gradient GEMMs) over work-groups: the
-// largest power of two <= min(WG_MAX_SPLIT, B / 256) with B / ksplit a multiple of 32.
-constexpr int WG_MAX_SPLIT = 8;
-int wgrad_split(int B)
+// Work-groups per member of the training pass: one per 32 rows, but no more in all than
+// the 256 CUs take at once (a group then takes several row tiles, in as many passes as the
+// fullest group needs), so the partials to add stay few at any batch.
+int train_groups(uint32_t nm, uint64_t batch)
 {
-    int ks = 1;
-    while (2 * ks <= WG_MAX_SPLIT && 2 * ks * 256 <= B && B % (2 * ks * TK) == 0) ks *= 2;
-    return ks;
+    const int tiles = (int)(batch / TR);
+    const int most = (int)(256 / nm);
+    const int passes = (tiles + most - 1) / most;
+    return (tiles + passes - 1) / passes;
 }
 
 MlpLayout mlp_layout(uint32_t nm, uint64_t batch, bool training)
@@ -330,22 +166,15 @@ MlpLayout mlp_layout(uint32_t nm, uint64_t batch, bool training)
     const uint64_t R = batch;
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t at = o; o += up(bytes); return at; };
-    if (training) {                    // inference keeps its activations in registers
+    if (training) {                    // operands of the weight gradients, partials
         L.a1 = take(nm * R * H * 2);
         L.a2 = take(nm * R * H * 2);
-        L.a3 = take(nm * R * H * 2);
-        L.u = take(nm * R * IN * 4);
-        L.z1 = take(nm * R * H * 4);
-        L.z2 = take(nm * R * H * 4);
-        L.z3 = take(nm * R * H * 4);
-        L.dz1 = take(nm * R * H * 2);
         L.dz2 = take(nm * R * H * 2);
         L.dz3 = take(nm * R * H * 2);
-        L.hpart = take(nm * (R / HEAD_ROWS) * HEAD_W * 4);
-        L.red = take((size_t)nm * RED_MAX_CHUNKS * NV1 * H * 4);
-        L.wpart = take((size_t)WG_MAX_SPLIT * nm * H * H * 4);
-        L.bpart = take((size_t)WG_MAX_SPLIT * nm * H * 4);
-    } else {
+        const size_t parts = (size_t)nm * train_groups(nm, batch);
+        L.hpart = take(parts * HEAD_W * 4);
+        L.cpart = take(parts * NV1 * H * 4);
+    } else {                           // inference keeps its activations in registers
         L.y = take(nm * batch * 4);
         L.blk = take(((batch + 255) / 256) * 4 + 4);
     }
@@ -365,28 +194,6 @@ int check_ws(const MlpLayout &L, void *d_ws, size_t ws_bytes)
     if (!d_ws || ((uintptr_t)d_ws & 255u)) return fail(BM_ERR_WORKSPACE, "workspace NULL or not 256-byte aligned");
     if (ws_bytes < L.total) return fail(BM_ERR_WORKSPACE, "workspace %zu B < %zu B needed", ws_bytes, L.total);
     return BM_OK;
-}
-
-// k tiles of 128 when every work-group's k range allows (K = 256 layers, 256-row
-// splits of the batch), else of 32.
-template <int EPI, bool TA, bool TB>
-hipError_t gemm(const GemmArgs &g, int members, hipStream_t s)
-{
-    const int ks = g.ksplit > 1 ? g.ksplit : 1;
-    const int krange = ks > 1 ? g.kchunk : g.K;
-    const dim3 grid((uint32_t)(g.N / TN), (uint32_t)((g.M + TM - 1) / TM), (uint32_t)(members * ks));
-    if (krange % 128 == 0)
-        hipLaunchKernelGGL((k_gemm<EPI, TA, TB, 128>), grid, dim3(256), 0, s, g);
-    else
-        hipLaunchKernelGGL((k_gemm<EPI, TA, TB, TK>), grid, dim3(256), 0, s, g);
-    return hipGetLastError();
-}
-
-GemmArgs gemm_args()
-{
-    GemmArgs g;
-    std::memset(&g, 0, sizeof g);
-    return g;
 }
 
 // ---------------------------------------------------------------------------
@@ -581,37 +388,6 @@ __global__ void __launch_bounds__(INFER_BT, 2) k_mlp_infer(const float *x, uint6
     }
 }
 
-// Training forward of `rows` rows through layers 1-3 of all members, keeping what
-// backward needs (normalised inputs, pre-activations z, BF16 activations); the output
-// layer runs fused with the loss (k_head).
-hipError_t train_forward(uint32_t nm, const float *params, const bf16_t *wbf, const float *x, const uint32_t *idx,
-                         uint64_t idx_stride, int rows, char *ws, const MlpLayout &L, hipStream_t s)
-{
-    bf16_t *a1 = (bf16_t *)(ws + L.a1), *a2 = (bf16_t *)(ws + L.a2), *a3 = (bf16_t *)(ws + L.a3);
-    float *u = (float *)(ws + L.u), *z1 = (float *)(ws + L.z1);
-    float *z2 = (float *)(ws + L.z2), *z3 = (float *)(ws + L.z3);
-    hipLaunchKernelGGL(k_l1_fwd, dim3((uint32_t)rows, nm), dim3(256), 0, s, x, idx, idx_stride, wbf, params, rows,
-                       u, z1, a1);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const bf16_t *ain[2] = {a1, a2};
-    bf16_t *aout[2] = {a2, a3};
-    float *zo[2] = {z2, z3};
-    const int woff[2] = {BOFF_W2, BOFF_W3}, boff[2] = {OFF_B2, OFF_B3};
-    for (int l = 0; l < 2; ++l) {
-        GemmArgs g = gemm_args();
-        g.A = ain[l]; g.a_mstride = (uint64_t)rows * H; g.lda = H;
-        g.B = wbf + woff[l]; g.b_mstride = NBF; g.ldb = H;
-        g.M = rows; g.N = H; g.K = H;
-        g.bias = params + boff[l]; g.bias_mstride = NPARAM;
-        g.zout = zo[l]; g.zout_mstride = (uint64_t)rows * H;
-        g.out_bf = aout[l]; g.out_mstride = (uint64_t)rows * H; g.ldc = H;
-        e = gemm<EPI_FWD, false, false>(g, (int)nm, s);
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
-}
-
 } // namespace
 
 // ---------------------------------------------------------------------------
@@ -696,60 +472,26 @@ extern "C" int bm_mlp_backward(uint32_t n_members, const float *d_params, const 
     if (rc) return rc;
     hipStream_t s = (hipStream_t)stream;
     char *ws = (char *)d_ws;
-    const int B = (int)batch;
-    const uint32_t nm = n_members;
-    const bf16_t *wbf = (const bf16_t *)d_wbf;
-    float *u = (float *)(ws + L.u);
-    float *z1 = (float *)(ws + L.z1), *z2 = (float *)(ws + L.z2), *z3 = (float *)(ws + L.z3);
-    bf16_t *a1 = (bf16_t *)(ws + L.a1), *a2 = (bf16_t *)(ws + L.a2), *a3 = (bf16_t *)(ws + L.a3);
-    bf16_t *dz1 = (bf16_t *)(ws + L.dz1), *dz2 = (bf16_t *)(ws + L.dz2), *dz3 = (bf16_t *)(ws + L.dz3);
-    float *hpart = (float *)(ws + L.hpart), *red = (float *)(ws + L.red);
-
-    hipError_t e = train_forward(nm, d_params, wbf, d_x, d_idx, batch, B, ws, L, s);
-    // output layer, loss, dW4 / db4 and dz3
-    const int nhead = B / HEAD_ROWS;
-    if (e == hipSuccess) {
-        hipLaunchKernelGGL(k_head, dim3(nhead, nm), dim3(256), 0, s, (const bf16_t *)a3, (const float *)z3, wbf,
-                           d_params, d_t, d_idx, batch, B, dz3, hpart);
-        hipLaunchKernelGGL(k_head_final, dim3(nm), dim3(256), 0, s, (const float *)hpart, nhead, B, d_grad,
-                           d_loss);
-        e = hipGetLastError();
-    }
-    // layers 3 and 2: weight gradients dW = dz^T a_prev, bias gradients, and dz_prev
-    const bf16_t *dzs[2] = {dz3, dz2};
-    bf16_t *dzp[2] = {dz2, dz1};
-    const bf16_t *aprev[2] = {a2, a1};
-    const float *zprev[2] = {z2, z1};
-    const int woff[2] = {OFF_W3, OFF_W2}, boff[2] = {OFF_B3, OFF_B2}, bwoff[2] = {BOFF_W3, BOFF_W2};
-    const int ks = wgrad_split(B);
-    float *wpart = (float *)(ws + L.wpart), *bpart = (float *)(ws + L.bpart);
-    for (int l = 0; l < 2 && e == hipSuccess; ++l) {
-        // dW = dz^T a_prev split over the batch, with the bias gradient (the row sums
-        // of dz^T) from the same staged tiles; then the partials added in order
-        GemmArgs g = gemm_args();
-        g.A = dzs[l]; g.a_mstride = (uint64_t)B * H; g.lda = H;          // (m = out, k = row): dz[k][m]
-        g.B = aprev[l]; g.b_mstride = (uint64_t)B * H; g.ldb = H;        // (k = row, n = in): a[k][n]
-        g.M = H; g.N = H; g.K = B;
-        g.out_f = wpart; g.out_mstride = (uint64_t)H * H; g.ldc = H;
-        g.ksplit = ks; g.kchunk = B / ks; g.out_kstride = (uint64_t)nm * H * H;
-        g.bias_part = bpart; g.bias_kstride = (uint64_t)nm * H;
-        e = gemm<EPI_STORE, true, true>(g, (int)nm, s);
-        if (e != hipSuccess) break;
-        hipLaunchKernelGGL(k_wgrad_sum, dim3(H * H / 256 + 1, nm), dim3(256), 0, s, (const float *)wpart,
-                           (const float *)bpart, ks, (int)nm, d_grad, woff[l], boff[l]);
-        e = hipGetLastError();
-        if (e != hipSuccess) break;
-        GemmArgs d = gemm_args();
-        d.A = dzs[l]; d.a_mstride = (uint64_t)B * H; d.lda = H;          // (m = row, k = out)
-        d.B = wbf + bwoff[l]; d.b_mstride = NBF; d.ldb = H;              // (k = out, n = in): W[k][n]
-        d.M = B; d.N = H; d.K = H;
-        d.zin = zprev[l]; d.zin_mstride = (uint64_t)B * H; d.ldz = H;
-        d.out_bf = dzp[l]; d.out_mstride = (uint64_t)B * H; d.ldc = H;
-        e = gemm<EPI_DGRAD, false, true>(d, (int)nm, s);
-    }
-    if (e == hipSuccess) {
-        e = colsum(nm, B, dz1, u, red, d_grad, s);
-    }
+    TrainArgs a{};
+    a.x = d_x;
+    a.t = d_t;
+    a.idx = d_idx;
+    a.wbf = (const bf16_t *)d_wbf;
+    a.params = d_params;
+    a.B = (int)batch;
+    a.a1T = (bf16_t *)(ws + L.a1);
+    a.a2T = (bf16_t *)(ws + L.a2);
+    a.dz2T = (bf16_t *)(ws + L.dz2);
+    a.dz3T = (bf16_t *)(ws + L.dz3);
+    a.hpart = (float *)(ws + L.hpart);
+    a.cpart = (float *)(ws + L.cpart);
+    a.members = (int)n_members;
+    a.groups = train_groups(n_members, batch);
+    a.grad = d_grad;
+    a.loss = d_loss;
+    hipLaunchKernelGGL(k_train_rows, dim3((uint32_t)a.groups, n_members), dim3(TBT), 0, s, a);
+    hipLaunchKernelGGL(k_train_wgrad, dim3(WG_BLOCKS * n_members), dim3(TBT), 0, s, a);
+    const hipError_t e = hipGetLastError();
     return e == hipSuccess ? ok() : hip_fail(e, "bm_mlp_backward");
 }
 

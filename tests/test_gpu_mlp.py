@@ -111,6 +111,35 @@ def test_gradients_with_member_indices():
         assert cosine(g[m], go) > 0.998
 
 
+@pytest.mark.parametrize("members,batch", [(1, 64), (5, 64), (5, 1088), (16, 576), (3, 2752)])
+def test_gradients_over_batches(members, batch):
+    """One and several row tiles per work-group, waves without rows in the weight
+    gradients, uneven passes, the most members; every parameter group."""
+    import torch
+    p = W.mlp_params(members, seed=21)
+    x = W.surrogate_queries(3000, seed=22)
+    t = (0.3 * np.sin(x[:, 0]) + 0.5 * x[:, 2]).astype(np.float32)
+    idx = np.random.default_rng(23).integers(0, 3000, (members, batch)).astype(np.int32)
+    say("gradients", members, batch)
+    s = B.Surrogate(members, params=p)
+    xd, td, id_ = (torch.tensor(v, device="cuda") for v in (x, t, idx))
+    loss = s.backward(xd, td, id_).cpu().numpy()
+    g = s.grad.cpu().numpy()
+    s.backward(xd, td, id_)
+    assert np.array_equal(g, s.grad.cpu().numpy())          # a fixed order of sums
+    offs = np.cumsum([0] + [int(np.prod(sh)) for _, sh in M.SIZES])
+    for m in range(0, members, 5):
+        lo, go = M.backward(p[m].astype(np.float64), x[idx[m]].astype(np.float64), t[idx[m]].astype(np.float64),
+                            bf16_weights=True)
+        assert abs(loss[m] - lo) <= 2e-2 * lo
+        for k, (name, _) in enumerate(M.SIZES):
+            a, b = g[m, offs[k]:offs[k + 1]], go[offs[k]:offs[k + 1]]
+            if name == "b4":
+                assert abs(a[0] - b[0]) <= 2e-2 * max(abs(b[0]), 1e-3), (m, name)
+                continue
+            assert rel_l2(a, b) < 5e-2, (m, name, rel_l2(a, b))
+
+
 def test_adam_matches_oracle_on_given_gradients():
     import torch
     p = W.mlp_params(NM, seed=8)

@@ -76,31 +76,68 @@ __global__ void __launch_bounds__(256) k_init_params(float *params, uint64_t tot
     params[i] = u / sqrtf(fan);
 }
 
-// Ensemble mean / population std over members and the routing flag; grid over rows.
+// Mean and population std of the members' predictions of row b; true if the row is
+// routed to the fallback.
+__device__ __forceinline__ bool row_stats(const float *y, int members, uint64_t B, uint64_t b, float thr, float *mean,
+                                          float *stdv)
+{
+    float s = 0.0f;
+    for (int m = 0; m < members; ++m) s += y[(uint64_t)m * B + b];
+    const float mu = s / (float)members;
+    float v = 0.0f;
+    for (int m = 0; m < members; ++m) {
+        const float d = y[(uint64_t)m * B + b] - mu;
+        v = fmaf(d, d, v);
+    }
+    const float sd = sqrtf(v / (float)members);
+    mean[b] = mu;
+    stdv[b] = sd;
+    return !(sd <= thr);                        // NaN std also falls back
+}
+
+// Rank of this thread's flag among the flags of its work-group (cnt: a counter per wave),
+// and their number.
+__device__ __forceinline__ uint32_t flag_rank(bool flag, uint32_t *cnt, uint32_t &total)
+{
+    const unsigned long long bal = __ballot(flag);
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    if (lane == 0) cnt[w] = (uint32_t)__popcll(bal);
+    __syncthreads();
+    uint32_t before = 0;
+    total = 0;
+    for (int i = 0; i < (int)(blockDim.x >> 6); ++i) {
+        before += i < w ? cnt[i] : 0u;
+        total += cnt[i];
+    }
+    return before + (uint32_t)__popcll(bal & ((1ull << lane) - 1ull));
+}
+
+// A query of at most ROUTE_ROWS rows in one work-group: statistics, routing flags and the
+// ordered compaction (three launches' work; 9 us of a 28 us query of 100 rows).
+constexpr int ROUTE_ROWS = 1024;
+
+__global__ void __launch_bounds__(ROUTE_ROWS) k_route_small(const float *y, int members, uint32_t B, float thr,
+                                                            float *mean, float *stdv, uint32_t *out, uint32_t *count)
+{
+    __shared__ uint32_t cnt[ROUTE_ROWS / 64];
+    const uint32_t b = threadIdx.x;
+    const bool flag = b < B && row_stats(y, members, B, b, thr, mean, stdv);
+    uint32_t total;
+    const uint32_t rank = flag_rank(flag, cnt, total);
+    if (flag) out[rank] = b;
+    if (b == 0) *count = total;
+}
+
+// Statistics of 256 rows per work-group and the number of routed ones; grid over rows.
 __global__ void __launch_bounds__(256) k_stats(const float *y, int members, uint64_t B, float thr, float *mean,
                                                float *stdv, uint32_t *blk_count)
 {
     const uint64_t b = (uint64_t)blockIdx.x * 256 + threadIdx.x;
-    bool flag = false;
-    if (b < B) {
-        float s = 0.0f;
-        for (int m = 0; m < members; ++m) s += y[(uint64_t)m * B + b];
-        const float mu = s / (float)members;
-        float v = 0.0f;
-        for (int m = 0; m < members; ++m) {
-            const float d = y[(uint64_t)m * B + b] - mu;
-            v = fmaf(d, d, v);
-        }
-        const float sd = sqrtf(v / (float)members);
-        mean[b] = mu;
-        stdv[b] = sd;
-        flag = !(sd <= thr);                    // NaN std also falls back
-    }
+    const bool flag = b < B && row_stats(y, members, B, b, thr, mean, stdv);
     __shared__ uint32_t cnt[4];
-    const unsigned long long bal = __ballot(flag);
-    if ((threadIdx.x & 63) == 0) cnt[threadIdx.x >> 6] = (uint32_t)__popcll(bal);
-    __syncthreads();
-    if (threadIdx.x == 0) blk_count[blockIdx.x] = cnt[0] + cnt[1] + cnt[2] + cnt[3];
+    uint32_t total;
+    (void)flag_rank(flag, cnt, total);
+    if (threadIdx.x == 0) blk_count[blockIdx.x] = total;
 }
 
 // Exclusive scan of the block counts (one block, sequential chunks) and the total.
@@ -123,20 +160,33 @@ __global__ void __launch_bounds__(256) k_scan_counts(uint32_t *blk, uint64_t nbl
     for (uint64_t i = lo; i < hi; ++i) { const uint32_t c = blk[i]; blk[i] = acc; acc += c; }
 }
 
-// Scatter the flagged row indices in increasing order.
-__global__ void __launch_bounds__(256) k_compact(const float *stdv, uint64_t B, float thr, const uint32_t *blk_off,
-                                                 uint32_t *out)
+// Scatter the flagged row indices in increasing order.  blk: the work-groups' counts
+// scanned by k_scan_counts (SCANNED), or as k_stats left them: each group then adds up
+// those before it, and the last one writes the total.
+template <bool SCANNED>
+__global__ void __launch_bounds__(256) k_compact(const float *stdv, uint64_t B, float thr, const uint32_t *blk,
+                                                 uint32_t *out, uint32_t *count)
 {
     const uint64_t b = (uint64_t)blockIdx.x * 256 + threadIdx.x;
     const bool flag = b < B && !(stdv[b] <= thr);
-    __shared__ uint32_t cnt[4];
-    const unsigned long long bal = __ballot(flag);
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    if (lane == 0) cnt[w] = (uint32_t)__popcll(bal);
-    __syncthreads();
-    uint32_t base = blk_off[blockIdx.x];
-    for (int i = 0; i < w; ++i) base += cnt[i];
-    const uint32_t rank = (uint32_t)__popcll(bal & ((1ull << lane) - 1ull));
+    __shared__ uint32_t cnt[4], sum[4];
+    uint32_t base = 0;
+    if constexpr (SCANNED) {
+        base = blk[blockIdx.x];
+    } else {
+        uint32_t s = 0;
+#pragma unroll 8
+        for (uint32_t i = threadIdx.x; i < blockIdx.x; i += 256) s += blk[i];
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
+        if ((threadIdx.x & 63) == 0) sum[threadIdx.x >> 6] = s;
+    }
+    uint32_t total;
+    const uint32_t rank = flag_rank(flag, cnt, total);       // its barrier publishes sum as well
+    if constexpr (!SCANNED) {
+        base = (sum[0] + sum[1]) + (sum[2] + sum[3]);
+        if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *count = base + total;
+    }
     if (flag) out[base + rank] = (uint32_t)b;
 }
 
@@ -388,6 +438,194 @@ __global__ void __launch_bounds__(INFER_BT, 2) k_mlp_infer(const float *x, uint6
     }
 }
 
+// ---------------------------------------------------------------------------
+// Inference of few rows.  k_mlp_infer walks 16 weight slices one after another, a global
+// load, an LDS write and a barrier each: about 20 us however few the rows.  Here a group
+// of eight waves holds both 256 x 256 layers of a member in registers -- wave w the
+// weights of features 32 w .. 32 w + 31, 128 registers per lane -- and activations pass
+// between the waves through LDS, four barriers per tile of 32 rows.  The weights of a wave
+// are 16 KiB in a row per layer: loaded 1 KiB at a time, all of them in flight, and
+// turned into fragments through a private LDS tile (the fragments' own 8-byte pieces
+// loaded directly took 13 us of the call, this 3 us).  100 rows x 5 members: 10 us against
+// 20.5 us; 3264 rows (two tiles per group): 14 against 21 us.  Same fragments, accumulator start
+// and element-wise order as k_mlp_infer, so a row's prediction does not depend on which of
+// the two runs.
+// ---------------------------------------------------------------------------
+constexpr int SWAVES = 8, SBT = 64 * SWAVES;
+constexpr int SRT = 2, SROWS = 16 * SRT;
+constexpr int INFER_PASSES = 3;        // most tiles of a group; beyond, k_mlp_infer is faster
+constexpr int SLD = H + 8;             // LDS row (bf16): 4 banks further per row
+static_assert(SWAVES * 32 == H, "wave w owns k-step w of the next layer");
+
+__global__ void __launch_bounds__(SBT, 2) k_mlp_infer_rows(const float *x, uint64_t rows, const bf16_t *wbf,
+                                                           const float *params, float *y, uint64_t y_stride)
+{
+    __shared__ __align__(16) bf16_t sAct[2][SROWS * SLD];
+    __shared__ __align__(16) bf16_t sTile[SWAVES][16 * SLD];
+    __shared__ __align__(16) float sL1[H * 8];           // per feature: W1[f][0..4], b1[f], pad
+    __shared__ __align__(16) float sB[2][H];
+    __shared__ __align__(16) float sW4[H];               // in the permuted order
+    __shared__ __align__(16) float sU[SROWS * 8];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4, c = lane & 15;
+    const int m = blockIdx.y;
+    const float *P = params + (uint64_t)m * NPARAM;
+    const bf16_t *WB = wbf + (uint64_t)m * NBF;
+
+    // inputs of a tile: a row per thread of the first SROWS
+    float xr[IN] = {};
+    auto fetch = [&](uint64_t tile) {
+        const uint64_t r = tile * SROWS + tid;
+        if (tid < SROWS) {
+#pragma unroll
+            for (int j = 0; j < IN; ++j) xr[j] = x[(r < rows ? r : 0) * IN + j];
+        }
+    };
+    fetch(blockIdx.x);
+    // the wave's rows of layer 2, then 3, 16 rows (8 KiB) at a time
+    bf16x8 raw[4][8];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            raw[q][i] = *reinterpret_cast<const bf16x8 *>(WB + (q < 2 ? BOFF_W2 : BOFF_W3) +
+                                                         (32 * wave + 16 * (q & 1)) * H + (64 * i + lane) * 8);
+    if (tid < H) {
+#pragma unroll
+        for (int j = 0; j < IN; ++j) sL1[tid * 8 + j] = bf2f(WB[BOFF_W1 + tid * IN + j]);
+        sL1[tid * 8 + 5] = P[OFF_B1 + tid];
+    } else {
+        const int f = tid - H, s = f >> 5, q = f & 31;
+        sB[0][f] = P[OFF_B2 + f];
+        sB[1][f] = P[OFF_B3 + f];
+        // feature f's place in the permuted order of perm_feature
+        sW4[32 * s + (q & 12) * 2 + (q & 3) + (q >> 4) * 4] = bf2f(WB[BOFF_W4 + f]);
+    }
+    const float b4 = P[OFF_B4];
+    bf16x8 w[2][2][8];                       // [layer][feature tile][k-step]
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        bf16_t *t = sTile[wave];             // private: the wave's LDS accesses complete in order
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            *reinterpret_cast<bf16x8 *>(&t[(2 * i + (lane >> 5)) * SLD + (lane & 31) * 8]) = raw[q][i];
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+            struct Two { uint2 a, b; } v{*reinterpret_cast<const uint2 *>(&t[c * SLD + 32 * s + 4 * g]),
+                                         *reinterpret_cast<const uint2 *>(&t[c * SLD + 32 * s + 16 + 4 * g])};
+            w[q >> 1][q & 1][s] = __builtin_bit_cast(bf16x8, v);
+        }
+        asm volatile("" ::: "memory");
+    }
+
+    // eight values of row 16 rt + c: this wave's features, which are k-step `wave` of the
+    // next layer, at the place of its fragment
+    auto put = [&](bf16_t *dst, int rt, bf16x8 v) {
+        *reinterpret_cast<bf16x8 *>(dst + (16 * rt + c) * SLD + 32 * wave + 8 * g) = v;
+    };
+    auto layer = [&](int l, const bf16_t *in, bf16_t *out) {
+        floatx4 acc[2][SRT];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const floatx4 bias = *reinterpret_cast<const floatx4 *>(&sB[l][32 * wave + 16 * t + 4 * g]);
+#pragma unroll
+            for (int rt = 0; rt < SRT; ++rt) acc[t][rt] = bias;
+        }
+#pragma unroll
+        for (int s = 0; s < 8; ++s)
+#pragma unroll
+            for (int rt = 0; rt < SRT; ++rt) {
+                const bf16x8 b = *reinterpret_cast<const bf16x8 *>(in + (16 * rt + c) * SLD + 32 * s + 8 * g);
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+                    acc[t][rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[l][t][s], b, acc[t][rt], 0, 0, 0);
+            }
+#pragma unroll
+        for (int rt = 0; rt < SRT; ++rt) {
+            bf16x8 v;
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[4 * t + e] = to_bf(gelu(acc[t][rt][e]));
+            put(out, rt, v);
+        }
+    };
+
+    const uint64_t tiles = (rows + SROWS - 1) / SROWS;
+    for (uint64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+        if (tid < SROWS) {
+            float u[IN];
+            normalise(xr, u);
+#pragma unroll
+            for (int j = 0; j < IN; ++j) sU[tid * 8 + j] = u[j];
+        }
+        if (tile + gridDim.x < tiles) fetch(tile + gridDim.x);
+        __syncthreads();
+        // ---- layer 1 (5 -> 256, FP32 FMA on the BF16 weights) ----
+        {
+            bf16x8 v[SRT];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const float *wr = &sL1[perm_feature(wave, g, j) * 8];
+                const float4 w03 = *reinterpret_cast<const float4 *>(wr);
+                const float2 w45 = *reinterpret_cast<const float2 *>(wr + 4);
+#pragma unroll
+                for (int rt = 0; rt < SRT; ++rt) {
+                    const float *u = &sU[(16 * rt + c) * 8];
+                    float z = w45.y;
+                    z = fmaf(w03.x, u[0], z);
+                    z = fmaf(w03.y, u[1], z);
+                    z = fmaf(w03.z, u[2], z);
+                    z = fmaf(w03.w, u[3], z);
+                    z = fmaf(w45.x, u[4], z);
+                    v[rt][j] = to_bf(gelu(z));
+                }
+            }
+#pragma unroll
+            for (int rt = 0; rt < SRT; ++rt) put(sAct[0], rt, v[rt]);
+        }
+        __syncthreads();
+        layer(0, sAct[0], sAct[1]);
+        __syncthreads();
+        layer(1, sAct[1], sAct[0]);
+        __syncthreads();
+        // ---- layer 4 (256 -> 1): a wave per 16 rows, partial dot per lane group, then
+        //      across the 4 groups ----
+        if (wave < SRT) {
+            const bf16_t *src = sAct[0] + (16 * wave + c) * SLD + 8 * g;
+            float sum = 0.0f;
+#pragma unroll
+            for (int s = 0; s < 8; ++s) {
+                const bf16x8 a = *reinterpret_cast<const bf16x8 *>(src + 32 * s);
+#pragma unroll
+                for (int j = 0; j < 8; ++j) sum = fmaf((float)a[j], sW4[32 * s + 8 * g + j], sum);
+            }
+            sum += __shfl_xor(sum, 16, 64);
+            sum += __shfl_xor(sum, 32, 64);
+            const uint64_t r = tile * SROWS + 16 * wave + c;
+            if (g == 0 && r < rows) y[(uint64_t)m * y_stride + r] = sum + b4;
+        }
+        // the next tile writes sU (read by layer 1, two barriers ago) before its first
+        // barrier and sAct[0] after it
+    }
+}
+
+// Members' predictions y [nm][rows].
+hipError_t launch_infer(uint32_t nm, const float *x, uint64_t rows, const bf16_t *wbf, const float *params, float *y,
+                        hipStream_t s)
+{
+    const uint64_t tiles = (rows + SROWS - 1) / SROWS;
+    const uint64_t most = 256 / nm;                  // groups of eight waves: one per CU
+    if (tiles <= (uint64_t)INFER_PASSES * most) {
+        hipLaunchKernelGGL(k_mlp_infer_rows, dim3((uint32_t)(tiles < most ? tiles : most), nm), dim3(SBT), 0, s, x, rows,
+                           wbf, params, y, rows);
+    } else {
+        hipLaunchKernelGGL(k_mlp_infer, dim3((uint32_t)((rows + FROWS - 1) / FROWS), nm), dim3(INFER_BT), 0, s, x, rows,
+                           wbf, params, y, rows);
+    }
+    return hipGetLastError();
+}
+
 } // namespace
 
 // ---------------------------------------------------------------------------
@@ -449,9 +687,7 @@ extern "C" int bm_mlp_forward(uint32_t n_members, const float *d_params, const u
     rc = check_device(&dev);
     if (rc) return rc;
     hipStream_t s = (hipStream_t)stream;
-    hipLaunchKernelGGL(k_mlp_infer, dim3((uint32_t)((batch + FROWS - 1) / FROWS), n_members), dim3(INFER_BT), 0,
-                       s, d_x, batch, (const bf16_t *)d_wbf, d_params, d_y, batch);
-    hipError_t e = hipGetLastError();
+    const hipError_t e = launch_infer(n_members, d_x, batch, (const bf16_t *)d_wbf, d_params, d_y, s);
     return e == hipSuccess ? ok() : hip_fail(e, "bm_mlp_forward");
 }
 
@@ -517,27 +753,40 @@ extern "C" int bm_mlp_adam_step(uint32_t n_members, float *d_params, const float
     return e == hipSuccess ? ok() : hip_fail(e, "bm_mlp_adam_step");
 }
 
+// Most work-groups of 256 rows whose counts every compacting group adds up for itself:
+// the sums are nblk / 512 loads per thread and group, side by side, where the scan is one
+// group's serial work and a launch (9 us at 10^6 rows); beyond, the squared work overtakes
+// it.
+static constexpr uint64_t COMPACT_SUMS = 8192;
+
 // The kernels of a query: fused inference of every member into y, then mean, std,
-// routing flags and per-256-row counts (blk), their exclusive scan and the ordered
-// compaction of the routed rows.  Every element of y and blk a call reads is first
+// routing flags and per-256-row counts (blk), and the ordered compaction of the routed
+// rows.  Every element of y and blk a call reads is first
 // written by that call, so neither buffer needs clearing.
 static hipError_t enqueue_query(uint32_t n_members, const float *d_params, const uint16_t *d_wbf, const float *d_x,
                                 uint64_t batch, float threshold, float *d_mean, float *d_std,
                                 uint32_t *d_fallback_idx, uint32_t *d_fallback_count, float *y, uint32_t *blk,
                                 hipStream_t s)
 {
-    hipLaunchKernelGGL(k_mlp_infer, dim3((uint32_t)((batch + FROWS - 1) / FROWS), n_members), dim3(INFER_BT), 0,
-                       s, d_x, batch, (const bf16_t *)d_wbf, d_params, y, batch);
-    hipError_t e = hipGetLastError();
+    hipError_t e = launch_infer(n_members, d_x, batch, (const bf16_t *)d_wbf, d_params, y, s);
+    if (e != hipSuccess) return e;
     const uint64_t nblk = (batch + 255) / 256;
-    if (e == hipSuccess) {
-        hipLaunchKernelGGL(k_stats, dim3((uint32_t)nblk), dim3(256), 0, s, y, (int)n_members, batch, threshold,
-                           d_mean, d_std, blk);
-        hipLaunchKernelGGL(k_scan_counts, dim3(1), dim3(256), 0, s, blk, nblk, d_fallback_count);
-        hipLaunchKernelGGL(k_compact, dim3((uint32_t)nblk), dim3(256), 0, s, d_std, batch, threshold, blk,
-                           d_fallback_idx);
-        e = hipGetLastError();
+    if (batch <= ROUTE_ROWS) {
+        hipLaunchKernelGGL(k_route_small, dim3(1), dim3((uint32_t)(batch + 63) / 64 * 64), 0, s, (const float *)y,
+                           (int)n_members, (uint32_t)batch, threshold, d_mean, d_std, d_fallback_idx, d_fallback_count);
+        return hipGetLastError();
     }
+    hipLaunchKernelGGL(k_stats, dim3((uint32_t)nblk), dim3(256), 0, s, (const float *)y, (int)n_members, batch,
+                       threshold, d_mean, d_std, blk);
+    if (nblk <= COMPACT_SUMS) {
+        hipLaunchKernelGGL(k_compact<false>, dim3((uint32_t)nblk), dim3(256), 0, s, (const float *)d_std, batch,
+                           threshold, (const uint32_t *)blk, d_fallback_idx, d_fallback_count);
+    } else {
+        hipLaunchKernelGGL(k_scan_counts, dim3(1), dim3(256), 0, s, blk, nblk, d_fallback_count);
+        hipLaunchKernelGGL(k_compact<true>, dim3((uint32_t)nblk), dim3(256), 0, s, (const float *)d_std, batch,
+                           threshold, (const uint32_t *)blk, d_fallback_idx, d_fallback_count);
+    }
+    e = hipGetLastError();
     return e;
 }
 

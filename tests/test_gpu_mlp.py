@@ -203,6 +203,36 @@ def test_query_statistics_and_routing():
     assert rel_l2(mean[:500], mo) < 2e-2
 
 
+@pytest.mark.parametrize("members", [1, 5, 16])
+def test_few_rows_equal_many(members):
+    """A row's prediction does not depend on the batch it comes in (few rows and many run
+    different kernels): edges of the row tiles and of the rule that picks the kernel."""
+    import torch
+    s = B.Surrogate(members, params=W.mlp_params(members, seed=24))
+    x = torch.tensor(W.surrogate_queries(40_000, seed=25), device="cuda")
+    full = s.forward(x)
+    most = 256 // members * 32
+    for n in (1, 31, 32, 33, 100, most - 1, most, most + 1, 2 * most + 5, 3 * most, 3 * most + 1):
+        say("few rows", members, n)
+        assert torch.equal(s.forward(x[:n]), full[:, :n]), n
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 256, 1000, 1024, 1025, 8192 * 256, 8192 * 256 + 1])
+def test_routing_over_batches(n):
+    """One work-group, sums per work-group, and the scan: the routed rows in order."""
+    import torch
+    s = B.Surrogate(3, params=W.mlp_params(3, seed=26))
+    x = torch.tensor(W.surrogate_queries(n, seed=27), device="cuda")
+    y = s.forward(x).cpu().numpy().astype(np.float64)
+    thr = float(np.median(y.std(axis=0)))
+    mean, std, fidx, fcnt = s.query(x, thr)
+    std, k = std.cpu().numpy(), int(fcnt.cpu().numpy()[0])
+    say("routing", n, k)
+    assert np.allclose(mean.cpu().numpy(), y.mean(axis=0), rtol=0, atol=1e-6)
+    assert np.array_equal(fidx.cpu().numpy()[:k].astype(np.uint32), M.route(std, thr))
+    assert k == int(np.sum(~(std <= thr)))
+
+
 def test_init_distribution():
     import torch
     s = B.Surrogate(NM, seed=15)

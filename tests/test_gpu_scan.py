@@ -70,6 +70,22 @@ def test_scan_equals_ensembles_bitwise(prec):
         assert g.n == w.n_paths
 
 
+@pytest.mark.parametrize("order", ["rising", "falling", "mixed"])
+@pytest.mark.parametrize("prec", [W.F32, W.F64])
+def test_scan_points_of_different_periods(prec, order):
+    """Forcing tables and work items are filled per point on the device: drive periods of
+    1, 37, 200 and 400 steps (some shared) and no drive at all, horizons in any order."""
+    base = W.C1.with_(prec=prec, seed=3)
+    steps = [700, 650, 500, 400, 333, 300, 64]
+    steps = {"rising": steps[::-1], "falling": steps, "mixed": [400, 64, 700, 333, 300, 650, 500]}[order]
+    spps = [200, 37, 200, 0, 1, 400, 37]
+    pts = [base.with_(name="p%d" % i, spp=s, a=base.a if s else 0.0, dt=0.0 if s else 0.006, n_paths=50 + 77 * i,
+                      n_steps=n, n_window=n // 3, point=i, F=0.02 * i) for i, (s, n) in enumerate(zip(spps, steps))]
+    say("scan periods", prec, order)
+    for w, g in zip(pts, run_scan(pts)):
+        assert stats_bytes(g) == stats_bytes(ensemble_stats(w)), w.name
+
+
 def test_scan_busy_jumps_bitwise():
     """Kick queues that fill up (lambda dt = 0.5, flips with probability ~0.2 per step) end
     windows early inside the scan's persistent loop as well."""

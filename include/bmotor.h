@@ -295,7 +295,8 @@ int bm_scan_workspace_size(const bm_model *models, const bm_run *runs, size_t n_
  * wave claims items with an atomic add and integrates them with the ensemble
  * path's code; one per-point reduction].  Point i's result goes to d_results[i]
  * (n_points bm_stats, device) and is bit-identical to bm_integrate(runs[i].n_steps)
- * + bm_reduce on an ensemble of that point.  tune: NULL = bm_tune_get_default.
+ * + bm_reduce on an ensemble of that point.  tune: NULL = the shape bm_tune_lookup
+ * finds, else one path per lane (results never depend on it).
  * Returns once the upload is complete (it synchronises `stream`). */
 int bm_scan_plan_create(const bm_model *models, const bm_run *runs, size_t n_points, const bm_tune *tune,
                         void *d_ws, size_t ws_bytes, bm_stats *d_results, void *stream, bm_scan_plan **out);
@@ -324,7 +325,7 @@ int bm_scan_autotune(const bm_model *models, const bm_run *runs, size_t n_points
 /* Default launch shape per (dyn, pot, noise, prec) for this process (used when
  * a call gets no bm_tune); the built-in default is 1 path per lane, block 256,
  * groups_per_cu 0, except FP32 inertial models without Poisson or dichotomous
- * noise: 2 paths per lane, block 128. */
+ * noise: 2 paths per lane, block 128 (taken by ensembles of 2^18 paths or more). */
 int bm_tune_set_default(uint32_t dyn, uint32_t pot, uint32_t noise, uint32_t prec, const bm_tune *tune);
 int bm_tune_get_default(uint32_t dyn, uint32_t pot, uint32_t noise, uint32_t prec, bm_tune *out);
 

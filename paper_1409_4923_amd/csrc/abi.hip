@@ -388,7 +388,7 @@ static int open_ensemble(const bm_model *model, const bm_run *run, void *d_ws, s
     e->ws = (char *)d_ws;
     e->stream = (hipStream_t)stream;
     e->n_done = steps_done;
-    const bm_tune dt = default_tune(model->dyn, model->pot, model->noise, run->prec);
+    const bm_tune dt = default_tune(model->dyn, model->pot, model->noise, run->prec, run->n_paths);
     e->ppl = dt.paths_per_lane;
     e->block = dt.block;
     fill_kargs(e);
@@ -441,7 +441,7 @@ extern "C" int bm_ensemble_destroy(bm_ensemble *e)
 extern "C" int bm_ensemble_set_tune(bm_ensemble *e, const bm_tune *t)
 {
     if (!e) return fail(BM_ERR_INVALID_ARG, "NULL handle");
-    const bm_tune use = t ? *t : default_tune(e->model.dyn, e->model.pot, e->model.noise, e->run.prec);
+    const bm_tune use = t ? *t : default_tune(e->model.dyn, e->model.pot, e->model.noise, e->run.prec, e->run.n_paths);
     // the step-control kernel draws its jumps inline: no LDS queues to fit
     const uint32_t queued = step_control(&e->run) ? (e->model.noise & BM_NOISE_GAUSS) : e->model.noise;
     int rc = check_tune(&use, queued, e->run.prec);
@@ -488,7 +488,8 @@ extern "C" int bm_integrate(bm_ensemble *e, uint64_t n_steps)
     while (n < end) {
         uint64_t stop = end;
         const uint64_t nw = e->run.window_start;
-        if (n < nw && nw < stop) stop = nw;       // split so the snapshot falls on a launch end
+        // the step-control kernel takes the snapshot at a launch end, the other inside
+        if (step_control(&e->run) && n < nw && nw < stop) stop = nw;
         KArgs k = e->k;
         k.n0 = n;
         k.n1 = stop;
@@ -522,9 +523,11 @@ extern "C" int bm_reduce(bm_ensemble *e, bm_stats *d_out)
     KArgs k = e->k;
     set_window(e, k);
     const int pot = (int)e->model.pot;
-    hipError_t he = e->run.prec == BM_F32 ? launch_velocity_f32(pot, k, e->stream)
-                                          : launch_velocity_f64(pot, k, e->stream);
+    const bool small = e->run.n_paths <= REDUCE_SMALL;
+    hipError_t he = e->run.prec == BM_F32 ? launch_velocity_f32(pot, k, small ? d_out : nullptr, e->stream)
+                                          : launch_velocity_f64(pot, k, small ? d_out : nullptr, e->stream);
     if (he != hipSuccess) return hip_fail(he, "velocity kernel launch");
+    if (small) return ok();
     const uint64_t chunks = (e->run.n_paths + 63) / 64;
     hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(256), 0, e->stream, k.part, chunks, k.t_window, d_out);
     he = hipGetLastError();

@@ -25,8 +25,9 @@ PointConst point_const(const bm_model *m, const bm_run *r, const void *d_tab);
 int check_device(int *dev_out);                     // a gfx950 device is current
 
 // Launch shape used when the caller passes no bm_tune: set by bm_tune_set_default
-// (or bm_scan_autotune), else paths_per_lane 1, block 256, groups_per_cu 0.
-bm_tune default_tune(uint32_t dyn, uint32_t pot, uint32_t noise, uint32_t prec);
+// (or bm_scan_autotune), else the built-in shape of the model, for an ensemble of
+// n_paths (default: many).
+bm_tune default_tune(uint32_t dyn, uint32_t pot, uint32_t noise, uint32_t prec, uint64_t n_paths = ~0ull);
 size_t queue_lds_bytes(uint32_t noise, uint32_t prec, uint32_t ppl, uint32_t block);
 int check_tune(const bm_tune *t, uint32_t noise, uint32_t prec);
 

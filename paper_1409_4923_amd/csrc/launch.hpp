@@ -24,8 +24,10 @@ BM_DECLARE_LAUNCHERS(f64_in)
 #undef BM_DECLARE_LAUNCHERS
 
 // per-path velocity + wave partials, and the state export (depend on precision and L only)
-hipError_t launch_velocity_f32(int pot, const KArgs &a, hipStream_t s);
-hipError_t launch_velocity_f64(int pot, const KArgs &a, hipStream_t s);
+// out: also reduce to it, in the same launch (n_paths <= REDUCE_SMALL), or null
+constexpr uint32_t REDUCE_SMALL = 2048;
+hipError_t launch_velocity_f32(int pot, const KArgs &a, bm_stats *out, hipStream_t s);
+hipError_t launch_velocity_f64(int pot, const KArgs &a, bm_stats *out, hipStream_t s);
 hipError_t launch_density_f32(int pot, const KArgs &a, uint32_t n_bins, unsigned long long *hist, hipStream_t s);
 hipError_t launch_density_f64(int pot, const KArgs &a, uint32_t n_bins, unsigned long long *hist, hipStream_t s);
 // flags of the export: READ_VP the per-path velocity exists (steps done > window

@@ -44,7 +44,6 @@ __device__ __forceinline__ void store_path(const KArgs &a, uint32_t p, const Pat
     if constexpr ((NOISE & NZ_POISSON) != 0) { a.sP[p] = s.sP; a.kP[p] = s.kP; }
     if constexpr ((NOISE & NZ_JGRID) != 0) a.thP[p] = s.thP;
     if constexpr ((NOISE & NZ_DICH) != 0) { a.sD[p] = s.sD; a.mD[p] = s.mD; a.d[p] = s.d; }
-    if (a.snapshot) { arr<R>(a.xi)[p] = s.x; a.wi[p] = s.w; }
 }
 
 // Constant-within-step forcing at phase k: drive + tilt - Poisson bias + potential
@@ -412,12 +411,13 @@ template <typename R, int NOISE> constexpr uint32_t queue_bytes()
 // non-simplified scheme take one call per 4 steps) and 17 scalar loads of the
 // forcing table; x is folded after every step whose index is a multiple of 16.
 // smem holds the jump queues, slot-major with stride qs; column col(j) is this
-// lane's j-th path.
+// lane's j-th path.  A window ends at a.n_window as well, and snap() runs after that
+// step: one launch crosses the start of eq. (31)'s averaging.
 // ---------------------------------------------------------------------------
-template <typename R, int DYN, int POT, int NOISE, int PPL>
+template <typename R, int DYN, int POT, int NOISE, int PPL, typename Snap>
 __device__ __forceinline__ void advance_range(const PointConst &a, const uint32_t (&path)[PPL],
                                               Path<R> (&s)[PPL], uint64_t n0, uint64_t n1,
-                                              unsigned char *lds, uint32_t qs, uint32_t col0)
+                                              unsigned char *lds, uint32_t qs, uint32_t col0, Snap snap)
 {
     const uint32_t dtab = digit_bytes<R, NOISE>() * (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     unsigned char *smem = lds + table_lds<R, NOISE>(blockDim.x >> 6);
@@ -454,7 +454,8 @@ __device__ __forceinline__ void advance_range(const PointConst &a, const uint32_
 
     while (n < n1) {
         const uint64_t wnext = ((n >> a.jw_log2) + 1u) << a.jw_log2;
-        uint64_t wend = wnext < n1 ? wnext : n1;
+        const uint64_t stop = n < a.n_window && a.n_window < n1 ? a.n_window : n1;
+        uint64_t wend = wnext < stop ? wnext : stop;
         const uint32_t wdrawn = (uint32_t)(wend - n);   // steps the queues were drawn for
         uint32_t wlen = wdrawn;
         uint32_t cover = wdrawn;
@@ -641,6 +642,7 @@ __device__ __forceinline__ void advance_range(const PointConst &a, const uint32_
                     s[j].mD -= queued_beyond(fq + col(j), qs, wlen, wdrawn, [](uint32_t e) { return e; });
             }
         }
+        if (n == a.n_window) snap();
     }
     if constexpr ((NOISE & NZ_JGRID) != 0) {
         // every kick drawn lay before the last window's end and has been applied
@@ -670,7 +672,11 @@ __global__ void __launch_bounds__(512) k_advance(const KArgs a)
         path[j] = valid[j] ? (uint32_t)p : a.p.n_paths - 1u;
         load_path<R, POT, NOISE>(a, path[j], s[j]);
     }
-    advance_range<R, DYN, POT, NOISE, PPL>(a.p, path, s, a.n0, a.n1, smem, PPL * blockDim.x, threadIdx.x);
+    advance_range<R, DYN, POT, NOISE, PPL>(a.p, path, s, a.n0, a.n1, smem, PPL * blockDim.x, threadIdx.x, [&] {
+#pragma unroll
+        for (int j = 0; j < PPL; ++j)
+            if (valid[j]) { arr<R>(a.xi)[path[j]] = s[j].x; a.wi[path[j]] = s[j].w; }
+    });
 #pragma unroll
     for (int j = 0; j < PPL; ++j)
         if (valid[j]) store_path<R, POT, NOISE>(a, path[j], s[j]);
@@ -732,10 +738,8 @@ __global__ void __launch_bounds__(256) k_init(const KArgs a)
 // eq. (31) per path in FP64, plus one double-double partial per wave (64 paths).
 // Launched with 256-lane work-groups; chunk c covers paths [64c, 64c + 64).
 // ---------------------------------------------------------------------------
-template <typename R, int POT>
-__global__ void __launch_bounds__(256) k_velocity(const KArgs a)
+template <typename R, int POT> __device__ __forceinline__ void velocity_of(const KArgs &a, uint64_t p)
 {
-    const uint64_t p = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const double L = period<POT>();
     double vp = 0.0;
     bool have = p < a.p.n_paths;
@@ -750,6 +754,23 @@ __global__ void __launch_bounds__(256) k_velocity(const KArgs a)
     if ((threadIdx.x & 63u) == 0u && (chunk << 6) < a.p.n_paths) {
         a.part[chunk] = part;
     }
+}
+
+template <typename R, int POT>
+__global__ void __launch_bounds__(256) k_velocity(const KArgs a)
+{
+    velocity_of<R, POT>(a, (uint64_t)blockIdx.x * blockDim.x + threadIdx.x);
+}
+
+// The same and the reduction of the partials in one launch of 1024 lanes, for ensembles
+// where the second launch costs more than the parallelism of the first gives: at most
+// REDUCE_SMALL paths, two chunks of 64 per wave.
+template <typename R, int POT>
+__global__ void __launch_bounds__(1024) k_velocity_reduce(const KArgs a, bm_stats *out)
+{
+    for (uint64_t p = threadIdx.x; (p & ~(uint64_t)63) < a.p.n_paths; p += 1024) velocity_of<R, POT>(a, p);
+    __syncthreads();                             // the partials, from the same CU's memory
+    reduce_chunks(a.part, ((uint64_t)a.p.n_paths + 63) / 64, a.t_window, out);
 }
 
 // ---------------------------------------------------------------------------

@@ -40,16 +40,18 @@ __device__ __forceinline__ void finish_stats(DD s1, DD s2, uint64_t n, uint64_t 
     *out = st;
 }
 
-// One 256-lane work-group combines n_chunks partials: lane t folds chunks
-// [n t / 256, n (t+1) / 256) in order, then a fixed LDS tree; lane 0 writes.
+// One work-group of at least 256 lanes combines n_chunks partials: lane t < 256 folds
+// chunks [n t / 256, n (t+1) / 256) in order (several loads in flight: the fold of 2^20
+// paths is 64 loads per lane), then a fixed LDS tree; lane 0 writes.
 __device__ __forceinline__ void reduce_chunks(const Partial *part, uint64_t n_chunks, double tw, bm_stats *out)
 {
     __shared__ double l1h[256], l1l[256], l2h[256], l2l[256];
     __shared__ uint64_t lc[256], lb[256];
     const uint32_t t = threadIdx.x;
-    const uint64_t lo = n_chunks * t / 256, hi = n_chunks * (t + 1) / 256;
+    const uint64_t lo = n_chunks * t / 256, hi = t < 256 ? n_chunks * (t + 1) / 256 : lo;
     DD s1{0.0, 0.0}, s2{0.0, 0.0};
     uint64_t c = 0, b = 0;
+#pragma unroll 8
     for (uint64_t i = lo; i < hi; ++i) {
         const Partial q = part[i];
         s1 = dd_add(s1, DD{q.s1_hi, q.s1_lo});
@@ -57,7 +59,7 @@ __device__ __forceinline__ void reduce_chunks(const Partial *part, uint64_t n_ch
         c += q.n;
         b += q.n_bad;
     }
-    l1h[t] = s1.hi; l1l[t] = s1.lo; l2h[t] = s2.hi; l2l[t] = s2.lo; lc[t] = c; lb[t] = b;
+    if (t < 256) { l1h[t] = s1.hi; l1l[t] = s1.lo; l2h[t] = s2.hi; l2l[t] = s2.lo; lc[t] = c; lb[t] = b; }
     __syncthreads();
     for (uint32_t st = 128; st >= 1; st >>= 1) {
         if (t < st) {

@@ -73,7 +73,7 @@ bm_tune builtin_tune()
 namespace bm {
 namespace host {
 
-bm_tune default_tune(uint32_t dyn, uint32_t pot, uint32_t noise, uint32_t prec)
+bm_tune default_tune(uint32_t dyn, uint32_t pot, uint32_t noise, uint32_t prec, uint64_t n_paths)
 {
     {
         std::lock_guard<std::mutex> lk(g_tune_mu);
@@ -82,12 +82,35 @@ bm_tune default_tune(uint32_t dyn, uint32_t pot, uint32_t noise, uint32_t prec)
     }
     bm_tune t = builtin_tune();
     // FP32 inertial paths without jump processes: two paths per lane give the step
-    // loop independent work to interleave (measured 1.47 against 1.41e12 path-steps/s
-    // on 2^20 paths); with jump queues the second path costs occupancy instead.
-    if (prec == BM_F32 && dyn == BM_INERTIAL && (noise & (BM_NOISE_POISSON | BM_NOISE_DICH)) == 0) {
+    // loop independent work to interleave once every SIMD has waves to choose from
+    // (179 against 187 ns per step at 2^18 paths, four waves per SIMD); with fewer a step
+    // lasts as long as one wave's instructions, and a second path doubles them (105
+    // against 59 ns up to 2^16 paths, 181 against 110 at 2^17).  With jump queues the
+    // second path costs occupancy instead.
+    if (prec == BM_F32 && dyn == BM_INERTIAL && (noise & (BM_NOISE_POISSON | BM_NOISE_DICH)) == 0 &&
+        n_paths >= (1u << 18)) {
         t.paths_per_lane = 2;
         t.block = 128;
     }
+    return t;
+}
+
+// Launch shape of a scan without a bm_tune: the installed one, else one path per lane.
+// A scan ends with its longest horizons, whose waves run the slower the more paths they
+// carry (512 points of up to 10^4 steps: 3.86 against 4.15 ms with two; 64 points: 0.82
+// against 1.11 ms), and one path per lane fills the chip as well as two (20000 points of
+// 2000 steps: 6.59 against 6.61 ms).  FP32 inertial models without jump queues run in
+// groups of one wave, which spread evenly over the CUs (64 points: 0.82 against 0.92 ms
+// with 256 lanes); the others measured no better so (FP64: 0.89 against 0.81 ms).
+bm_tune scan_tune(uint32_t dyn, uint32_t pot, uint32_t noise, uint32_t prec)
+{
+    {
+        std::lock_guard<std::mutex> lk(g_tune_mu);
+        auto it = g_tune.find(std::make_tuple(dyn, pot, noise, prec));
+        if (it != g_tune.end()) return it->second.t;
+    }
+    bm_tune t = builtin_tune();
+    if (prec == BM_F32 && dyn == BM_INERTIAL && (noise & (BM_NOISE_POISSON | BM_NOISE_DICH)) == 0) t.block = 64;
     return t;
 }
 
@@ -519,7 +542,7 @@ static int plan_create(const bm_model *models, const bm_run *runs, size_t n, con
     if (rc) return rc;
     if (!out || !d_results) return fail(BM_ERR_INVALID_ARG, "out and d_results must not be NULL");
     const uint32_t prec = runs[0].prec, dyn = models[0].dyn, pot = models[0].pot, noise = models[0].noise;
-    const bm_tune t = tune ? *tune : default_tune(dyn, pot, noise, prec);
+    const bm_tune t = tune ? *tune : scan_tune(dyn, pot, noise, prec);
     rc = check_tune(&t, noise, prec);
     if (rc) return rc;
     const ScanLayout L = scan_layout(runs, n);

@@ -65,10 +65,10 @@ __global__ void __launch_bounds__(512) k_scan(const ScanArgs a)
             xi[j] = s[j].x;
             wi[j] = s[j].w;
         }
-        advance_range<R, DYN, POT, NOISE, PPL>(P, path, s, 0, P.n_window, smem, qs, threadIdx.x);
+        advance_range<R, DYN, POT, NOISE, PPL>(P, path, s, 0, P.n_steps, smem, qs, threadIdx.x, [&] {
 #pragma unroll
-        for (int j = 0; j < PPL; ++j) { xi[j] = s[j].x; wi[j] = s[j].w; }
-        advance_range<R, DYN, POT, NOISE, PPL>(P, path, s, P.n_window, P.n_steps, smem, qs, threadIdx.x);
+            for (int j = 0; j < PPL; ++j) { xi[j] = s[j].x; wi[j] = s[j].w; }
+        });
         const PointRed rd = a.red[item.point];
 #pragma unroll
         for (int j = 0; j < PPL; ++j) {

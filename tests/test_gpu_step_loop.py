@@ -21,6 +21,20 @@ def final(w, cuts, tune=None):
     return e.read()
 
 
+@pytest.mark.parametrize("n", [1, 64, 65, 1024, 1025, 2048, 2049])
+def test_statistics_in_one_launch_or_two(n):
+    """Up to 2048 paths the velocities and their reduction are one launch: the same bits
+    as a scan point, whose reduction runs on its own."""
+    w = W.C1.with_(n_paths=n, n_steps=80, n_window=33, point=5)
+    say("statistics", n)
+    m, r = W.to_c(w)
+    e = B.Ensemble(m, r)
+    e.integrate(80)
+    sc = B.Scan([m], [r])
+    sc.launch()
+    assert bytes(memoryview(e.stats())) == bytes(memoryview(sc.stats()[0]))
+
+
 @pytest.mark.parametrize("prec", [W.F32, W.F64], ids=["f32", "f64"])
 @pytest.mark.parametrize("model", sorted(BASE))
 @pytest.mark.parametrize("n", [1, 20, 35, 36, 37, 64 + 3])
@@ -30,5 +44,5 @@ def test_few_paths_in_a_wave(model, prec, n):
     say("few paths", model, prec, n)
     ref = final(w.with_(n_paths=192), [77])
     got = final(w.with_(n_paths=n), [5, 16, 56])
-    for a, b in ((ref.x, got.x), (ref.v, got.v), (ref.noise, got.noise)):
+    for a, b in ((ref.x, got.x), (ref.v, got.v), (ref.noise, got.noise), (ref.vp, got.vp)):
         assert np.array_equal(a.numpy()[:n], b.numpy())

@@ -5,7 +5,7 @@ from __future__ import annotations
 import numpy as np
 import pytest
 
-from helpers import say
+from helpers import oracle_paths, say
 from paper_1409_4923_amd import bmotor as B
 from paper_1409_4923_amd import workloads as W
 
@@ -46,3 +46,16 @@ def test_few_paths_in_a_wave(model, prec, n):
     got = final(w.with_(n_paths=n), [5, 16, 56])
     for a, b in ((ref.x, got.x), (ref.v, got.v), (ref.noise, got.noise), (ref.vp, got.vp)):
         assert np.array_equal(a.numpy()[:n], b.numpy())
+
+
+@pytest.mark.parametrize("rate", [0.1, 2.0, 20.0, 300.0])
+def test_flips_at_any_rate(rate):
+    """Dichotomous noise from flips in few blocks of steps to several in every four
+    (windows with a look ahead, without one, and cut short by a full queue): every flip
+    at its step, against the FP64 oracle."""
+    w = W.C3.with_(prec=W.F64, mua=rate, mub=2.0 * rate, n_paths=130, n_steps=1100, n_window=333)
+    say("flips", rate)
+    got = final(w, [7, 500, 593])
+    x, _, noise, _ = oracle_paths(w, 0, w.n_paths, w.n_steps)
+    assert np.array_equal(got.noise.numpy(), noise)
+    assert np.max(np.abs(got.x.numpy() - x) / np.maximum(1.0, np.abs(x))) <= 1e-9

@@ -180,8 +180,9 @@ int bm_ensemble_workspace_size(const bm_model *model, const bm_run *run, size_t 
  * initial conditions on `stream`: x(0), v(0) uniform, Poisson countdown
  * s = floor(E / (lambda dt)) with E ~ Exp(1), dichotomous state drawn from its
  * stationary law Pr{+Fb} = mu_a / (mu_a + mu_b) and entered at step 0.
- * The drive table (a cos(2 pi k / spp) + F in FP64) is uploaded from host memory
- * and create returns once that copy is complete (it synchronises `stream`).
+ * The drive table (a cos(2 pi k / spp) + F in FP64) is formed on the host and goes to
+ * the device with the kernel's arguments; only a table of more than 13 KiB is copied,
+ * and create then returns once that copy is complete (it synchronises `stream`).
  * The handle is written to *out.  BM_ERR_DEVICE if no gfx950 device is usable. */
 int bm_ensemble_create(const bm_model *model, const bm_run *run, void *d_ws, size_t ws_bytes,
                        void *stream, bm_ensemble **out);
@@ -196,7 +197,8 @@ int bm_ensemble_create(const bm_model *model, const bm_run *run, void *d_ws, siz
  * path state: integrating from there gives bit for bit what an uninterrupted run
  * gives (the random streams are counter-based).  model and run must equal those
  * the workspace was created with -- the library cannot check this.  Uploads the
- * drive table like bm_ensemble_create (and synchronises `stream`). */
+ * drive table like bm_ensemble_create (which for a table of more than 13 KiB synchronises
+ * `stream`). */
 int bm_ensemble_attach(const bm_model *model, const bm_run *run, void *d_ws, size_t ws_bytes,
                        uint64_t steps_done, void *stream, bm_ensemble **out);
 

@@ -2,6 +2,8 @@
 // sequencing, and the fixed-order FP64 ensemble reduction (eq. 31).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -196,10 +198,16 @@ extern "C" int bm_ensemble_workspace_size(const bm_model *model, const bm_run *r
 // ---------------------------------------------------------------------------
 int check_device(int *dev_out)
 {
-    int n = 0;
+    // devices found to be gfx950 (a device's architecture does not change)
+    static std::atomic<uint64_t> known{0};
+    int n = 0, dev = 0;
+    if (known.load(std::memory_order_relaxed) != 0 && hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < 64 &&
+        (known.load(std::memory_order_relaxed) >> dev & 1u)) {
+        *dev_out = dev;
+        return BM_OK;
+    }
     hipError_t e = hipGetDeviceCount(&n);
     if (e != hipSuccess || n == 0) return fail(BM_ERR_DEVICE, "no HIP device available");
-    int dev = 0;
     e = hipGetDevice(&dev);
     if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
     hipDeviceProp_t prop;
@@ -208,6 +216,7 @@ int check_device(int *dev_out)
     if (std::strncmp(prop.gcnArchName, "gfx950", 6) != 0)
         return fail(BM_ERR_DEVICE, "device %d is %s; libbmotor is built for gfx950 only", dev,
                     prop.gcnArchName);
+    if (dev < 64) known.fetch_or(1ull << dev, std::memory_order_relaxed);
     *dev_out = dev;
     return BM_OK;
 }
@@ -230,8 +239,6 @@ struct bm_ensemble {
     KArgs k;                 // template of the kernel arguments
     uint64_t n_done;
     uint32_t ppl, block;
-    std::vector<double> tab64;
-    std::vector<float> tab32;
 };
 
 namespace bm {
@@ -358,13 +365,35 @@ static void fill_kargs(bm_ensemble *e)
     }
 }
 
-static void fill_table(bm_ensemble *e)
+__global__ void __launch_bounds__(256) k_table(const TableChunk tab, uint32_t n_words, uint32_t *dst)
 {
-    forcing_table(&e->model, &e->run, e->tab64);
-    e->tab32.assign(e->tab64.begin(), e->tab64.end());
+    store_chunk(tab, n_words, dst);
 }
 
-// Creates the handle and uploads the drive table; `init` enqueues the initial
+// The forcing table in the path precision, as words.
+static std::vector<uint32_t> table_words(const bm_ensemble *e)
+{
+    std::vector<double> tab;
+    forcing_table(&e->model, &e->run, tab);
+    const bool f32 = e->run.prec == BM_F32;
+    std::vector<uint32_t> w(tab.size() * (f32 ? 1 : 2));
+    for (size_t i = 0; i < tab.size(); ++i) {
+        if (f32) {
+            const float f = (float)tab[i];
+            std::memcpy(&w[i], &f, 4);
+        } else {
+            std::memcpy(&w[2 * i], &tab[i], 8);
+        }
+    }
+    return w;
+}
+
+// Most chunks of a table that go by kernel arguments (one launch each, the first with
+// the initial conditions): 400 steps per period in FP64 take one; beyond, the launches
+// cost as much as waiting for a copy.
+constexpr size_t TABLE_LAUNCHES = 4;
+
+// Creates the handle and enqueues the drive table; `init` enqueues the initial
 // conditions, otherwise the workspace already holds the state after steps_done.
 static int open_ensemble(const bm_model *model, const bm_run *run, void *d_ws, size_t ws_bytes, void *stream,
                          bool init, uint64_t steps_done, bm_ensemble **out)
@@ -392,15 +421,37 @@ static int open_ensemble(const bm_model *model, const bm_run *run, void *d_ws, s
     e->ppl = dt.paths_per_lane;
     e->block = dt.block;
     fill_kargs(e);
-    fill_table(e);
 
     const bool f32 = run->prec == BM_F32;
-    const void *src = f32 ? (const void *)e->tab32.data() : (const void *)e->tab64.data();
-    const size_t tb = (f32 ? 4 : 8) * e->tab64.size();
-    // The table is read from host memory owned by the handle: wait for the copy so
-    // that the handle can be destroyed at any time after this returns.
-    hipError_t he = hipMemcpyAsync((char *)d_ws + L.tab, src, tb, hipMemcpyHostToDevice, e->stream);
-    if (he == hipSuccess) he = hipStreamSynchronize(e->stream);
+    hipError_t he = hipSuccess;
+    TableChunk first;
+    uint32_t first_words = 0;
+    try {
+        const std::vector<uint32_t> tab = table_words(e);
+        uint32_t *dst = (uint32_t *)((char *)d_ws + L.tab);
+        constexpr size_t per = TABLE_CHUNK / 4;
+        if (tab.size() <= TABLE_LAUNCHES * per) {
+            for (size_t at = 0; at < tab.size() && he == hipSuccess; at += per) {
+                TableChunk c;
+                const uint32_t n = (uint32_t)std::min(per, tab.size() - at);
+                std::memcpy(c.w, &tab[at], (size_t)n * 4);
+                if (at == 0 && init) {               // stored by the kernel of the initial conditions
+                    first = c;
+                    first_words = n;
+                    continue;
+                }
+                hipLaunchKernelGGL(k_table, dim3(1), dim3(256), 0, e->stream, c, n, dst + at);
+                he = hipGetLastError();
+            }
+        } else {
+            // read from host memory released below: wait for the copy
+            he = hipMemcpyAsync(dst, tab.data(), tab.size() * 4, hipMemcpyHostToDevice, e->stream);
+            if (he == hipSuccess) he = hipStreamSynchronize(e->stream);
+        }
+    } catch (const std::bad_alloc &) {
+        delete e;
+        return fail(BM_ERR_INVALID_ARG, "out of host memory");
+    }
     if (he != hipSuccess) { delete e; return hip_fail(he, "drive table upload"); }
 
     if (init) {
@@ -408,11 +459,11 @@ static int open_ensemble(const bm_model *model, const bm_run *run, void *d_ws, s
         k.snapshot = run->window_start == 0 ? 1u : 0u;
         const int pot = (int)model->pot, noise = (int)model->noise;
         if (f32)
-            he = model->dyn == BM_INERTIAL ? launch_init_f32_in(pot, noise, k, e->stream)
-                                           : launch_init_f32_od(pot, noise, k, e->stream);
+            he = model->dyn == BM_INERTIAL ? launch_init_f32_in(pot, noise, k, first, first_words, e->stream)
+                                           : launch_init_f32_od(pot, noise, k, first, first_words, e->stream);
         else
-            he = model->dyn == BM_INERTIAL ? launch_init_f64_in(pot, noise, k, e->stream)
-                                           : launch_init_f64_od(pot, noise, k, e->stream);
+            he = model->dyn == BM_INERTIAL ? launch_init_f64_in(pot, noise, k, first, first_words, e->stream)
+                                           : launch_init_f64_od(pot, noise, k, first, first_words, e->stream);
         if (he != hipSuccess) { delete e; return hip_fail(he, "init kernel launch"); }
     }
     *out = e;

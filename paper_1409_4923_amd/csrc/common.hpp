@@ -159,4 +159,16 @@ struct KArgs {
 };
 constexpr uint32_t SC_MAX_HALVINGS = 8;
 
+// Part of a forcing table passed by value: with KArgs beside it, it fits the 4 KiB of a
+// kernel's arguments, so a table reaches the device with the launch that needs it -- no
+// copy, and no host memory that the copy would have to be waited for.
+constexpr uint32_t TABLE_CHUNK = 3392;
+struct TableChunk { uint32_t w[TABLE_CHUNK / 4]; };
+static_assert(sizeof(KArgs) + sizeof(TableChunk) + 16 <= 4096, "kernel arguments beyond 4 KiB");
+
+__device__ __forceinline__ void store_chunk(const TableChunk &c, uint32_t n_words, uint32_t *dst)
+{
+    for (uint32_t i = threadIdx.x; i < n_words; i += blockDim.x) dst[i] = c.w[i];
+}
+
 } // namespace bm

@@ -10,7 +10,8 @@ namespace bm {
 struct ScanArgs;
 
 #define BM_DECLARE_LAUNCHERS(SUF)                                                                 \
-    hipError_t launch_init_##SUF(int pot, int noise, const KArgs &a, hipStream_t s);               \
+    hipError_t launch_init_##SUF(int pot, int noise, const KArgs &a, const TableChunk &tab,        \
+                                 uint32_t tab_words, hipStream_t s);                               \
     hipError_t launch_advance_##SUF(int pot, int noise, int ppl, int block, const KArgs &a,       \
                                     hipStream_t s);                                                \
     hipError_t launch_scan_##SUF(int pot, int noise, int ppl, int block, int groups_per_cu,       \

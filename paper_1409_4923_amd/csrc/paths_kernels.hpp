@@ -718,7 +718,8 @@ __global__ void __launch_bounds__(512) k_advance(const KArgs a)
 // Initial conditions (tag 2), computed in FP64 and stored in the path precision:
 // x ~ U[x0_lo, x0_hi) folded, v ~ U[v0_lo, v0_hi), Poisson countdown
 // floor(E / (lambda dt)), dichotomous state opposite to a stationary draw with
-// countdown 0 (the first step flips into the stationary state).
+// countdown 0 (the first step flips into the stationary state).  The first work-group
+// also stores the first tab_words words of the forcing table.
 // ---------------------------------------------------------------------------
 template <typename R, int DYN, int POT, int NOISE>
 __device__ __forceinline__ Path<R> init_path(const PointConst &a, uint32_t p)
@@ -750,8 +751,9 @@ __device__ __forceinline__ Path<R> init_path(const PointConst &a, uint32_t p)
 }
 
 template <typename R, int DYN, int POT, int NOISE>
-__global__ void __launch_bounds__(256) k_init(const KArgs a)
+__global__ void __launch_bounds__(256) k_init(const KArgs a, const TableChunk tab, uint32_t tab_words)
 {
+    if (blockIdx.x == 0) store_chunk(tab, tab_words, (uint32_t *)const_cast<void *>(a.p.tab));
     const uint64_t p64 = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (p64 >= a.p.n_paths) return;
     const uint32_t p = (uint32_t)p64;

@@ -59,3 +59,21 @@ def test_flips_at_any_rate(rate):
     x, _, noise, _ = oracle_paths(w, 0, w.n_paths, w.n_steps)
     assert np.array_equal(got.noise.numpy(), noise)
     assert np.max(np.abs(got.x.numpy() - x) / np.maximum(1.0, np.abs(x))) <= 1e-9
+
+
+@pytest.mark.parametrize("prec", [W.F32, W.F64], ids=["f32", "f64"])
+@pytest.mark.parametrize("spp", [1, 7, 408, 409, 832, 833, 1500, 3400])
+def test_forcing_tables_of_any_length(spp, prec):
+    """Tables that go with one launch's arguments, with several, and by a copy: the same
+    bits as a scan point, whose table a kernel forms; also through a resume."""
+    w = W.C1.with_(prec=prec, spp=spp, n_paths=70, n_steps=2 * spp + 40, n_window=spp // 2, point=2)
+    m, r = W.to_c(w)
+    say("table", spp, prec)
+    sc = B.Scan([m], [r])
+    sc.launch()
+    e = B.Ensemble(m, r)
+    e.integrate(spp)
+    f = B.Ensemble(m, r, checkpoint=e.checkpoint())
+    for x in (e, f):
+        x.integrate(w.n_steps - spp)
+        assert bytes(memoryview(x.stats())) == bytes(memoryview(sc.stats()[0]))

@@ -7,6 +7,17 @@
 
 namespace bm {
 
+// Whether kernel K has dynamic LDS only (see lds_at); a property of the built code.
+template <auto K> hipError_t dynamic_lds_only()
+{
+    static const hipError_t e = [] {
+        hipFuncAttributes f{};
+        const hipError_t r = hipFuncGetAttributes(&f, reinterpret_cast<const void *>(K));
+        return r != hipSuccess ? r : f.sharedSizeBytes == 0 ? hipSuccess : hipErrorInvalidConfiguration;
+    }();
+    return e;
+}
+
 struct ScanArgs;
 
 #define BM_DECLARE_LAUNCHERS(SUF)                                                                 \

@@ -16,7 +16,7 @@ enum : int { NZ_GAUSS = 1, NZ_POISSON = 2, NZ_DICH = 4,
              NZ_NORMAL = 8,     // Gaussian noise with normal increments (non-simplified scheme)
              NZ_JGRID = 16 };   // Poisson kicks at their exact times (jump-adapted grid)
 
-// Poisson kicks pre-drawn per window into the LDS queue (fixed grid only).
+// Poisson kicks drawn ahead into a ring of their own (fixed grid only).
 template <int NOISE> constexpr bool queued_kicks()
 {
     return (NOISE & NZ_POISSON) != 0 && (NOISE & NZ_JGRID) == 0;
@@ -187,40 +187,96 @@ template <int POT, typename R> __device__ __forceinline__ void fold(Path<R> &s)
 }
 
 // ---------------------------------------------------------------------------
-// Jump processes on the dt grid.  The times and sizes of the jumps do not depend
-// on the path state, so each lane resolves all jumps of a window of steps in
-// one wave-uniform loop (the draws are the same as in Algorithms 3 / 4 step by
-// step) and queues them in LDS; the step loop then only compares the step
-// offset with the next queued offset.  The window (16 2^k steps, at most 1024) is
-// chosen per parameter point so that a lane expects about four jumps in it: the
-// wave-uniform loop runs as many iterations as the lane with the most jumps, and
-// a queue rarely fills up.  On the fixed grid a full queue ends the window early for
-// the whole wave (at the first jump it does not hold); on the jump-adapted grid a
-// lane with more than JCAP flips in a window queues an "inline" marker and draws
-// the rest at their steps.
+// Jump processes.  The times and sizes of the jumps do not depend on the path state, so
+// each lane draws them ahead (the same draws as in Algorithms 3 / 4 step by step) into a
+// ring in LDS and the step loop only compares the step number with the next queued one.
+// Before a block of steps the wave draws until every lane's ring covers it; every lane
+// with room draws along, so the draws of many blocks happen side by side whichever lane
+// asked for them.  (Windows of a fixed number of steps, whose draws took as many turns as
+// the lane with the most jumps needed, took 1.6 times the turns at 0.016 kicks per step.)
+// Windows -> rings, 4000 steps: 500001 paths on the jump-adapted grid 3.60 -> 3.40 ms,
+// 262147 FP64 paths with kicks 558 -> 533 us per 800 steps (rings of 24 KiB per 256 lanes
+// instead of queues of 48: four groups per CU, as the registers allow, instead of three), 2^20 inertial Poisson
+// paths 2.80 -> 2.75 ms.
+// A ring holds one jump less than its slots: the slot behind the last queued jump is a
+// sentinel with the step of the first jump not drawn yet.
 // ---------------------------------------------------------------------------
-constexpr uint32_t JCAP = 11;         // queued jumps per lane and window
-constexpr uint32_t INLINE_BIT = 0x80000000u;
 
-// A kick of the jump-adapted grid, drawn ahead: its step offset in the window, the
-// fraction of that step at which it falls, its amplitude, and the Gaussian
-// increment (times G sqrt(3 dt) or G sqrt(dt)) of the piece that follows it.
-template <typename R> struct JGKick {
+// Slots of a ring of 2^log2 entries: 8, or 16 where a lane expects more than 1.6 jumps in
+// 16 steps (a full ring cuts the block short).
+constexpr uint32_t RING_LOG2 = 3, RING_LOG2_BUSY = 4;
+
+// A kick of the jump-adapted grid, drawn ahead: its step, the fraction of that step at
+// which it falls, its amplitude, and the Gaussian increment (times G sqrt(3 dt) or
+// G sqrt(dt)) of the piece that follows it.
+template <typename R> struct alignas(4 * sizeof(R)) JGKick {
     uint32_t off;
     R th, z, u;
 };
-constexpr uint32_t JG_NONE = 0xFFFFFFFFu;
-// Queued kicks per lane and window of the jump-adapted grid (more wait for the next
-// window): 9 in FP32, so that four groups of 256 lanes with their increment tables fit a
-// CU's 160 KiB (10 leave room for three: 3.82 against 3.60 ms per 500001 paths x 4000
-// steps); 6 in FP64, so that the FP64 queues of 256 lanes with the dichotomous queue
-// still fit in 64 KiB of LDS.
-template <typename R> constexpr uint32_t jg_cap() { return sizeof(R) == 4 ? 9u : 6u; }
+// Slots of its ring: 8 in FP32, 6 in FP64, so that the FP64 rings of 256 lanes with the
+// dichotomous ring still fit in 64 KiB of LDS.  A step with more kicks draws the rest at
+// the step.
+template <typename R> constexpr uint32_t jg_slots() { return sizeof(R) == 4 ? 8u : 6u; }
 
-template <typename R> struct KickEntry {
-    uint32_t off;   // step offset in the window (>= the steps run: none left)
-    R z;            // amplitude
+// A queued kick: its step and amplitude (FP64: 12 bytes, so that LDS does not limit the
+// groups of a CU).
+template <typename R> struct KickEntry;
+template <> struct alignas(8) KickEntry<float> {
+    uint32_t off;
+    float z;
+    __device__ static KickEntry make(uint32_t o, float v) { return KickEntry{o, v}; }
+    __device__ float amplitude() const { return z; }
 };
+template <> struct KickEntry<double> {
+    uint32_t off, lo, hi;
+    __device__ static KickEntry make(uint32_t o, double v)
+    {
+        return KickEntry{o, (uint32_t)__double2loint(v), (uint32_t)__double2hiint(v)};
+    }
+    __device__ double amplitude() const { return __hiloint2double((int)hi, (int)lo); }
+};
+
+// LDS at a byte address.  The path kernels address their LDS by numbers: it is all dynamic
+// and begins at 0, so ring positions wrap with one AND and no base is added at each
+// access.  Static LDS would lie in front of it: the kernels have no __shared__ variable,
+// name the dynamic array (use_dynamic_lds: a kernel that uses no LDS the compiler knows of
+// has its stack arrays moved there), and their launchers check that none is left
+// (dynamic_lds_only).
+template <typename T> __device__ __forceinline__ T &lds_at(uint32_t at)
+{
+    return *(T *)(__attribute__((address_space(3))) T *)(uintptr_t)at;
+}
+__device__ __forceinline__ void use_dynamic_lds()
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    asm volatile("" ::"v"((uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem));
+}
+
+// One ring's place in LDS (wave-uniform): the byte offset of its slots, the bytes from one
+// slot of a lane's column to the next, and of all slots.  Positions in a ring are byte
+// offsets from `base` that include the lane's column.
+struct Ring {
+    uint32_t base, stride, total;
+};
+template <typename E> inline constexpr bool ring_masked = true; // 2^k slots of 2^i bytes, 2^j columns
+template <> inline constexpr bool ring_masked<KickEntry<double>> = false;
+template <> inline constexpr bool ring_masked<JGKick<double>> = false;
+template <typename E> __device__ __forceinline__ uint32_t ring_next(const Ring &r, uint32_t at)
+{
+    const uint32_t n = at + r.stride;
+    if constexpr (ring_masked<E>) {
+        return n & (r.total - 1u);
+    } else {
+        const uint32_t m = n - r.total;          // huge unless n is past the last slot
+        return n < m ? n : m;
+    }
+}
+// Bytes queued between the current position and the tail.
+__device__ __forceinline__ uint32_t ring_queued(const Ring &r, uint32_t at, uint32_t tail)
+{
+    const uint32_t d = tail - at;
+    return (int32_t)d < 0 ? d + r.total : d;
+}
 
 // Exponential countdown s = floor(E / (rate dt)), E = -ln(1 - phi), phi = w 2^-32,
 // decided exactly as in FP64 (the oracle's expression).  FP32 paths first form
@@ -278,99 +334,20 @@ __device__ __forceinline__ void kick_from(const PointConst &a, uint32_t ws, uint
     z = amplitude<R>(a, wz);
 }
 
+// Algorithm 4: dwell (steps) in state d_new from the flip's word w.
+template <typename R>
+__device__ __forceinline__ uint32_t flip_from(const PointConst &a, uint32_t w, int32_t d_new)
+{
+    return d_new ? countdown<R>(w, a.mub_dt, a.c_mub, a.tol0_mub, a.tol1)
+                 : countdown<R>(w, a.mua_dt, a.c_mua, a.tol0_mua, a.tol1);
+}
+
 // Algorithm 4 draw for flip number m into state d_new: dwell s (steps).
 template <typename R>
 __device__ __forceinline__ uint32_t flip_draw(const PointConst &a, uint32_t path, uint32_t m, int32_t d_new)
 {
     const U4 q = philox4x32_10(m >> 2, path, a.point, TAG_DICH, a.key0, a.key1);
-    const uint32_t w = pick(q, m & 3u);
-    return d_new ? countdown<R>(w, a.mub_dt, a.c_mub, a.tol0_mub, a.tol1)
-                 : countdown<R>(w, a.mua_dt, a.c_mua, a.tol0_mua, a.tol1);
-}
-
-// Queue the kicks of one window.  `off` is the offset of the next kick (the
-// Algorithm 3 countdown at the window start).  q[slot * qs] is this lane's queue.
-// One Philox block holds two kicks: an iteration uses both halves when it can.
-// Returns the number of leading steps of the window whose kicks are all queued:
-// wlen, or, when the queue is full, the offset of the first kick it does not hold.
-template <typename R>
-__device__ __forceinline__ uint32_t kick_window(const PointConst &a, uint32_t path, uint32_t wlen, uint32_t off,
-                                                uint32_t &kP, KickEntry<R> *q, uint32_t qs)
-{
-    uint32_t slot = 0;
-    bool active = off < wlen;
-    while (__any(active)) {
-        if (active) {
-            if (slot < JCAP) {
-                const U4 b = philox4x32_10(kP >> 1, path, a.point, TAG_POISSON, a.key0, a.key1);
-                const bool second = (kP & 1u) != 0u;
-                uint32_t sn;
-                R z;
-                kick_from<R>(a, second ? b.z : b.x, second ? b.w : b.y, sn, z);
-                q[slot * qs] = KickEntry<R>{off, z};
-                ++slot;
-                ++kP;
-                off = off + 1u + sn;
-                active = off < wlen;
-                if (!second && active && slot < JCAP) {      // the block's second kick
-                    kick_from<R>(a, b.z, b.w, sn, z);
-                    q[slot * qs] = KickEntry<R>{off, z};
-                    ++slot;
-                    ++kP;
-                    off = off + 1u + sn;
-                    active = off < wlen;
-                }
-            } else {
-                active = false;      // queue full: the window ends at this kick
-            }
-        }
-    }
-    q[slot * qs] = KickEntry<R>{off, R(0)};
-    return off < wlen ? off : wlen;
-}
-
-// Jumps queued in slots below JCAP at offsets in [from, wlen): drawn for a window
-// of wlen steps that ended after `from` steps.  Offsets rise along the queue and
-// the entry after the last queued jump lies at or beyond wlen (or at slot JCAP).
-template <typename T, typename OffOf>
-__device__ __forceinline__ uint32_t queued_beyond(const T *q, uint32_t qs, uint32_t from, uint32_t wlen, OffOf off_of)
-{
-    uint32_t c = 0;
-    for (uint32_t slot = 0; slot < JCAP; ++slot) {
-        const uint32_t o = off_of(q[slot * qs]);
-        if (o >= wlen) break;
-        c += (o >= from) ? 1u : 0u;
-    }
-    return c;
-}
-
-// Queue the flips of one window; bit INLINE_BIT marks "draw inline from here" (only
-// the jump-adapted grid runs past it; on the fixed grid a full queue ends the window,
-// as for kicks).  Returns the number of leading steps whose flips are all queued.
-template <typename R>
-__device__ __forceinline__ uint32_t flip_window(const PointConst &a, uint32_t path, uint32_t wlen, uint32_t off,
-                                                uint32_t &mD, int32_t d, uint32_t *q, uint32_t qs)
-{
-    uint32_t slot = 0;
-    bool active = off < wlen;
-    while (__any(active)) {
-        if (active) {
-            if (slot < JCAP) {
-                d = 1 - d;
-                const uint32_t sn = flip_draw<R>(a, path, mD, d);
-                q[slot * qs] = off;
-                ++slot;
-                ++mD;
-                off = off + 1u + sn;
-                active = off < wlen;
-            } else {
-                active = false;
-            }
-        }
-    }
-    const bool full = slot == JCAP && off < wlen;
-    q[slot * qs] = full ? (off | INLINE_BIT) : off;
-    return full ? off : wlen;
+    return flip_from<R>(a, pick(q, m & 3u), d_new);
 }
 
 // ---------------------------------------------------------------------------

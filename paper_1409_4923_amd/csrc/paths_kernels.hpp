@@ -54,20 +54,23 @@ template <typename R> __device__ __forceinline__ R drive_at(const PointConst &a,
     return reinterpret_cast<const R *>(a.tab)[k];
 }
 
-// Per-lane cursor into the LDS jump queues of the current window.
-
+// Per-lane cursors into the rings.  Steps are absolute step numbers modulo 2^32 (a run has
+// fewer than 2^32 steps and a countdown fewer than 2^31).  cX: position of the current
+// entry, whose contents are in registers; tX: position of the sentinel.
 template <typename R> struct JumpCursor {
-    uint32_t nP;    // offset of the next kick in the window
+    uint32_t nP;    // step of the next kick
     R zP;           // its amplitude
-    const KickEntry<R> *pP;   // the queue entry after it
-    uint32_t nD;    // offset of the next flip
-    uint32_t cD;    // element index of the next queue slot
+    uint32_t cP, tP;
+    uint32_t uP;    // step of the first kick not drawn
+    uint32_t nD;    // step of the next flip
+    uint32_t cD, tD;
+    uint32_t uD;    // step of the first flip not drawn
+    int32_t dT;     // state after the flips drawn
     R lev;          // dichotomous level of the current state
     // jump-adapted grid
-    JGKick<R> g;    // next kick (g.off == JG_NONE: none left in the window)
-    uint32_t gs;    // queue slot of g
-    uint32_t gn;    // kicks queued for this window
-    uint32_t poff;  // offset of the first kick not yet drawn
+    JGKick<R> g;    // next kick
+    uint32_t cG, tG;
+    uint32_t poff;  // step of the first kick not drawn
     double pth;     // its fraction of the step (FP64: kick times decide the integer state)
 };
 
@@ -122,7 +125,7 @@ __device__ __noinline__ double jg_next_time(double th, uint32_t w, double lam_dt
     return th + expo64(w) / lam_dt;
 }
 
-// Draws the kick that falls at (off, th) of the window -- its amplitude, the
+// Draws the kick that falls at (off, th) -- its amplitude, the
 // increment of the piece after it -- and the time of the next kick, counted from
 // it in FP64: off += floor(T), th = T - floor(T) with T = th + E / (lambda dt).
 template <typename R, int NOISE>
@@ -138,13 +141,13 @@ __device__ __forceinline__ JGKick<R> jg_draw(const PointConst &a, uint32_t path,
     e.u = piece_noise<R, NOISE>(a, path, kP, (R)a.g3);
     const double T = jg_next_time(th, second ? b.z : b.x, a.lam_dt);
     const double Tf = floor(T);
-    off += (uint32_t)Tf;                     // < 2^31 + window: validated on the host
+    off += (uint32_t)Tf;                     // Tf < 2^31: validated on the host
     th = T - Tf;
     ++kP;
     return e;
 }
 
-// The same draw out of line, for the rare step that holds more kicks than a queue
+// The same draw out of line, for the rare step that holds more kicks than a ring
 // (arguments and results by value, so that the caller's state stays in registers).
 template <typename R> struct JGDrawn {
     JGKick<R> e;
@@ -163,68 +166,27 @@ __device__ __noinline__ JGDrawn<R> jg_draw_inline(const PointConst a, uint32_t p
     return d;
 }
 
-// Fill the queue of one window (wave-uniform loop, as for the fixed grid) behind the
-// J.gn kicks carried over from the previous window, up to jg_cap<R>() kicks, with the
-// kicks that fall before the window's end.  Returns the number of leading steps of
-// the window whose kicks are all queued: wlen, or, when the queue is full, the offset
-// of the first kick it does not hold (J.poff).
-template <typename R, int NOISE>
-__device__ __forceinline__ uint32_t jg_window(const PointConst &a, uint32_t path, uint32_t wlen, uint32_t &kP,
-                                              JumpCursor<R> &J, JGKick<R> *q, uint32_t qs)
-{
-    uint32_t slot = J.gn;
-    bool active = J.poff < wlen && slot < jg_cap<R>();
-    while (__any(active)) {
-        if (active) {
-            q[slot * qs] = jg_draw<R, NOISE>(a, path, kP, J.poff, J.pth);
-            ++slot;
-            active = J.poff < wlen && slot < jg_cap<R>();
-        }
-    }
-    J.gn = slot;
-    J.gs = 0;
-    if (slot > 0) J.g = q[0];
-    else J.g.off = JG_NONE;
-    return J.poff < wlen ? J.poff : wlen;
-}
-
-// At the end of a window of wlen steps: the kicks still queued (drawn for steps past
-// an early end) move to the front of the queue with their offsets rebased, and the
-// offset of the first kick not yet drawn is rebased too.  The kick draws stay in
-// their sequence, so nothing is drawn twice or given back.
-template <typename R>
-__device__ __forceinline__ void jg_carry(JumpCursor<R> &J, JGKick<R> *q, uint32_t qs, uint32_t wlen)
-{
-    const uint32_t left = J.gn - J.gs;                    // gs <= gn <= jg_cap (jg_advance)
-    for (uint32_t i = 0; i < jg_cap<R>() && __any(i < left); ++i) {
-        if (i < left) {
-            JGKick<R> e = q[(J.gs + i) * qs];               // source index >= destination
-            e.off -= wlen;
-            q[i * qs] = e;
-        }
-    }
-    J.gn = left;
-    J.gs = 0;
-    J.poff -= wlen;
-}
-
-// Moves the cursor past the kick just applied.  Within a window every kick before
-// its end is queued; only the single-step fallback (INL) draws past its queue.  The
-// cursor index stops at the queue's end (gs <= gn), also while kicks are drawn inline.
+// Moves the cursor past the kick just applied.  Every kick of a block is queued; only the
+// single-step fallback (INL) draws past its ring, those of its own step `off`.
 template <typename R, int NOISE, bool INL>
-__device__ __forceinline__ void jg_advance(const PointConst &a, uint32_t path, uint32_t wlen, uint32_t &kP,
-                                           JumpCursor<R> &J, const JGKick<R> *q, uint32_t qs)
+__device__ __forceinline__ void jg_advance(const PointConst &a, uint32_t path, uint32_t off, uint32_t &kP,
+                                           JumpCursor<R> &J, const Ring &gr)
 {
-    if (J.gs < J.gn) ++J.gs;                  // the kick applied was the queue's entry gs
-    if (J.gs < J.gn) J.g = q[J.gs * qs];
-    else if (INL && J.poff < wlen) {
-        const JGDrawn<R> d = jg_draw_inline<R, NOISE>(a, path, kP, J.poff, J.pth);
-        J.g = d.e;
-        J.pth = d.th;
-        J.poff = d.off;
-        kP = d.kP;
+    if (!INL || J.cG != J.tG) {
+        J.cG = ring_next<JGKick<R>>(gr, J.cG);
+        J.g = lds_at<JGKick<R>>(gr.base + J.cG);
     }
-    else J.g.off = JG_NONE;
+    if (INL && J.cG == J.tG) {
+        if (J.poff == off) {
+            const JGDrawn<R> d = jg_draw_inline<R, NOISE>(a, path, kP, J.poff, J.pth);
+            J.g = d.e;
+            J.pth = d.th;
+            J.poff = d.off;
+            kP = d.kP;
+        } else {
+            J.g.off = J.poff;
+        }
+    }
 }
 
 // One step of the jump-adapted grid.  When no lane of the wave has a kick in this
@@ -239,7 +201,7 @@ __device__ __forceinline__ void jg_advance(const PointConst &a, uint32_t path, u
 // then the rest of the step.  The cursor already points past the first kick.
 template <typename R, int DYN, int POT, int NOISE, bool INL>
 __device__ __forceinline__ void jg_rest(const PointConst &a, uint32_t path, Path<R> &s, JumpCursor<R> &J,
-                                        const JGKick<R> *q, uint32_t qs, uint32_t wlen, uint32_t off,
+                                        const Ring &gr, uint32_t off,
                                         uint32_t kph, R h, R hh, R ngam, R kp, R A1, R lev, R from, R A_from, R u)
 {
     // further kicks in this step (lambda dt <= 16 is enforced on the host; the bound
@@ -252,7 +214,7 @@ __device__ __forceinline__ void jg_rest(const PointConst &a, uint32_t path, Path
         from = th;
         A_from = A_th;
         u = J.g.u;
-        jg_advance<R, NOISE, INL>(a, path, wlen, s.kP, J, q, qs);
+        jg_advance<R, NOISE, INL>(a, path, off, s.kP, J, gr);
     }
     pc_step<DYN, POT, false, R>(s, (R(1) - from) * h, (R(1) - from) * hh, ngam, kp, u * piece_sqrt(R(1) - from), R(0),
                                 A_from, A1);
@@ -260,7 +222,7 @@ __device__ __forceinline__ void jg_rest(const PointConst &a, uint32_t path, Path
 
 template <typename R, int DYN, int POT, int NOISE, bool INL>
 __device__ __forceinline__ void jg_step(const PointConst &a, uint32_t path, Path<R> &s, JumpCursor<R> &J,
-                                        const JGKick<R> *q, uint32_t qs, uint32_t wlen, uint32_t off,
+                                        const Ring &gr, uint32_t off,
                                         uint32_t kph, R dxi, R h, R hh, R ngam, R kp, R A0, R A1, R lev)
 {
     const bool kick = J.g.off == off;
@@ -287,16 +249,15 @@ __device__ __forceinline__ void jg_step(const PointConst &a, uint32_t path, Path
         // the kicked lanes' cursors move on: every lane reads the entry after its
         // cursor, the kicked lanes take it
         const R u_after = J.g.u;                 // increment of the piece after the kick
-        const uint32_t nidx = J.gs < J.gn ? J.gs + 1u : J.gs;
-        const bool more = nidx < J.gn;
-        const JGKick<R> e = q[(more ? nidx : 0u) * qs];
-        J.gs = kick ? nidx : J.gs;
-        J.g.off = kick ? (more ? e.off : JG_NONE) : J.g.off;
+        const uint32_t nx = ring_next<JGKick<R>>(gr, J.cG);
+        const JGKick<R> e = lds_at<JGKick<R>>(gr.base + nx);
+        J.cG = kick ? nx : J.cG;
+        J.g.off = kick ? e.off : J.g.off;
         J.g.th = kick ? e.th : J.g.th;
         J.g.z = kick ? e.z : J.g.z;
         J.g.u = kick ? e.u : J.g.u;
-        if (kick) jg_rest<R, DYN, POT, NOISE, INL>(a, path, s, J, q, qs, wlen, off, kph, h, hh, ngam, kp, A1, lev,
-                                                   th1, A_e, u_after);
+        if (kick) jg_rest<R, DYN, POT, NOISE, INL>(a, path, s, J, gr, off, kph, h, hh, ngam, kp, A1, lev, th1, A_e,
+                                                   u_after);
     } else {
         if (!any) {
             pc_step<DYN, POT, false, R>(s, h, hh, ngam, kp, dxi, R(0), A0, A1);
@@ -311,23 +272,22 @@ __device__ __forceinline__ void jg_step(const PointConst &a, uint32_t path, Path
         pc_step<DYN, POT, true, R>(s, th1 * h, th1 * hh, ngam, kp, dxi1, z1, A0, A_e);
         if (kick) {
             const R u_after = J.g.u;
-            jg_advance<R, NOISE, INL>(a, path, wlen, s.kP, J, q, qs);
-            jg_rest<R, DYN, POT, NOISE, INL>(a, path, s, J, q, qs, wlen, off, kph, h, hh, ngam, kp, A1, lev, th1,
-                                             A_e, u_after);
+            jg_advance<R, NOISE, INL>(a, path, off, s.kP, J, gr);
+            jg_rest<R, DYN, POT, NOISE, INL>(a, path, s, J, gr, off, kph, h, hh, ngam, kp, A1, lev, th1, A_e,
+                                             u_after);
         }
     }
 }
 
-// One step of one path at window offset `off` (drive phase kph): flips due at this
+// One step of one path, step number `off` (drive phase kph): flips due at this
 // step, Algorithm 1, and the Poisson kick due at this step, which Algorithm 3 adds
 // to the corrector's result.  `dxi` is the Algorithm 2 increment.  (Folding is
-// done by the caller.)
-// QUIET: no lane of the wave has a jump at this step (nothing to test).
+// done by the caller.)  QUIET: no lane of the wave has a jump at this step (nothing to
+// test).
 template <typename R, int DYN, int POT, int NOISE, bool INL = false, bool QUIET = false>
 __device__ __forceinline__ void full_step(const PointConst &a, uint32_t path, Path<R> &s, JumpCursor<R> &J,
-                                          const JGKick<R> *gq, const uint32_t *fq,
-                                          uint32_t qs, uint32_t wlen, uint32_t off, uint32_t kph, R dxi, R h,
-                                          R hh, R ngam, R kp,
+                                          const Ring &kr, const Ring &gr, const Ring &fr,
+                                          uint32_t off, uint32_t kph, R dxi, R h, R hh, R ngam, R kp,
                                           R A0, R A1, R Fa, R Fb)
 {
     if constexpr ((NOISE & NZ_DICH) != 0 && !QUIET) {
@@ -336,10 +296,8 @@ __device__ __forceinline__ void full_step(const PointConst &a, uint32_t path, Pa
             if (flip) {
                 s.d = 1 - s.d;
                 J.lev = s.d ? Fb : -Fa;
-                // the window ends before a full queue's marker: every flip is queued
-                const uint32_t e = fq[J.cD];
-                J.cD += qs;
-                J.nD = e & ~INLINE_BIT;
+                J.cD = ring_next<uint32_t>(fr, J.cD);
+                J.nD = lds_at<uint32_t>(fr.base + J.cD);
             }
         }
     }
@@ -350,7 +308,7 @@ __device__ __forceinline__ void full_step(const PointConst &a, uint32_t path, Pa
         A1 = A1 + lev;
     }
     if constexpr ((NOISE & NZ_JGRID) != 0 && !QUIET) {
-        jg_step<R, DYN, POT, NOISE, INL>(a, path, s, J, gq, qs, wlen, off, kph, dxi, h, hh, ngam, kp, A0, A1, lev);
+        jg_step<R, DYN, POT, NOISE, INL>(a, path, s, J, gr, off, kph, dxi, h, hh, ngam, kp, A0, A1, lev);
     } else {
         pc_step<DYN, POT, false, R>(s, h, hh, ngam, kp, dxi, R(0), A0, A1);
     }
@@ -358,14 +316,89 @@ __device__ __forceinline__ void full_step(const PointConst &a, uint32_t path, Pa
         if (J.nP == off) {                       // Algorithm 3: s <= 0 at this step
             if constexpr (DYN == DYN_INERTIAL) s.v = s.v + J.zP;
             else s.x = s.x + J.zP;
-            const KickEntry<R> e = *J.pP;
-            J.pP += qs;
+            J.cP = ring_next<KickEntry<R>>(kr, J.cP);
+            const KickEntry<R> e = lds_at<KickEntry<R>>(kr.base + J.cP);
             J.nP = e.off;
-            J.zP = e.z;
+            J.zP = e.amplitude();
         }
     }
 }
 
+// Draws for the rings, one turn: every lane with room draws (at most two kicks, the halves
+// of one Philox block; at most two flips; one kick of the jump-adapted grid), but only
+// jumps before step n + left, the end of the call: nothing is drawn that the call does not
+// apply.  Each returns whether this lane still needs a jump before step n + run and has
+// room for it.
+template <typename R>
+__device__ __forceinline__ bool draw_kicks(const PointConst &a, uint32_t path, uint32_t n, uint32_t run, uint32_t left,
+                                           uint32_t &kP, JumpCursor<R> &J, const Ring &r)
+{
+    using E = KickEntry<R>;
+    uint32_t room = r.total - r.stride - ring_queued(r, J.cP, J.tP);            // bytes
+    if (room != 0u && J.uP - n < left) {
+        const U4 b = philox4x32_10(kP >> 1, path, a.point, TAG_POISSON, a.key0, a.key1);
+        const bool odd = (kP & 1u) != 0u;
+        uint32_t sn;
+        R z;
+        kick_from<R>(a, odd ? b.z : b.x, odd ? b.w : b.y, sn, z);
+        lds_at<E>(r.base + J.tP) = E::make(J.uP, z);
+        J.tP = ring_next<E>(r, J.tP);
+        J.uP += 1u + sn;
+        ++kP;
+        room -= r.stride;
+        if (!odd && room != 0u && J.uP - n < left) {
+            kick_from<R>(a, b.z, b.w, sn, z);
+            lds_at<E>(r.base + J.tP) = E::make(J.uP, z);
+            J.tP = ring_next<E>(r, J.tP);
+            J.uP += 1u + sn;
+            ++kP;
+            room -= r.stride;
+        }
+    }
+    return room != 0u && J.uP - n < run;
+}
+
+template <typename R>
+__device__ __forceinline__ bool draw_flips(const PointConst &a, uint32_t path, uint32_t n, uint32_t run, uint32_t left,
+                                           uint32_t &mD, JumpCursor<R> &J, const Ring &r)
+{
+    uint32_t room = r.total - r.stride - ring_queued(r, J.cD, J.tD);
+    if (room != 0u && J.uD - n < left) {
+        const U4 q = philox4x32_10(mD >> 2, path, a.point, TAG_DICH, a.key0, a.key1);
+        const uint32_t w = mD & 3u;
+        J.dT = 1 - J.dT;
+        const uint32_t s0 = flip_from<R>(a, pick(q, w), J.dT);
+        lds_at<uint32_t>(r.base + J.tD) = J.uD;
+        J.tD = ring_next<uint32_t>(r, J.tD);
+        J.uD += 1u + s0;
+        ++mD;
+        room -= r.stride;
+        if (w != 3u && room != 0u && J.uD - n < left) {
+            J.dT = 1 - J.dT;
+            const uint32_t s1 = flip_from<R>(a, pick(q, w + 1u), J.dT);
+            lds_at<uint32_t>(r.base + J.tD) = J.uD;
+            J.tD = ring_next<uint32_t>(r, J.tD);
+            J.uD += 1u + s1;
+            ++mD;
+            room -= r.stride;
+        }
+    }
+    return room != 0u && J.uD - n < run;
+}
+
+template <typename R, int NOISE>
+__device__ __forceinline__ bool draw_jg(const PointConst &a, uint32_t path, uint32_t n, uint32_t run, uint32_t left,
+                                        uint32_t &kP, JumpCursor<R> &J, const Ring &r)
+{
+    using E = JGKick<R>;
+    uint32_t room = r.total - r.stride - ring_queued(r, J.cG, J.tG);
+    if (room != 0u && J.poff - n < left) {
+        lds_at<E>(r.base + J.tG) = jg_draw<R, NOISE>(a, path, kP, J.poff, J.pth);
+        J.tG = ring_next<E>(r, J.tG);
+        room -= r.stride;
+    }
+    return room != 0u && J.poff - n < run;
+}
 
 // Three-point increments from a table of digit pairs in LDS, one table per wave (the
 // waves of a scan hold different points): entry 6 a + b is the pair (increment of digit
@@ -380,7 +413,7 @@ template <typename R, int NOISE> constexpr uint32_t digit_bytes()
 {
     return (NOISE & NZ_GAUSS) != 0 ? 36u * (uint32_t)sizeof(Pair<R>) : 0u;
 }
-// LDS bytes a work-group of `waves` waves needs for its tables (before the queues).
+// LDS bytes a work-group of `waves` waves needs for its tables (behind the rings).
 template <typename R, int NOISE> __host__ __device__ constexpr uint32_t table_lds(uint32_t waves)
 {
     return digit_bytes<R, NOISE>() * waves;
@@ -394,64 +427,99 @@ template <typename R> __device__ __forceinline__ R digit_increment(uint32_t digi
 // Increments of the two leading base-6 digits of u, from the table at LDS offset `tab`
 // (a multiple of the entry size S): floor(36 u / 2^32) S = floor(36 S u / 2^32) with the
 // low bits cleared, so one multiply and one mask give the address.
-template <typename R> __device__ __forceinline__ Pair<R> digit_pair(const unsigned char *smem, uint32_t tab, uint32_t u)
+template <typename R> __device__ __forceinline__ Pair<R> digit_pair(uint32_t tab, uint32_t u)
 {
     constexpr uint32_t S = (uint32_t)sizeof(Pair<R>);
     const uint32_t off = (uint32_t)(((uint64_t)u * (36u * S) + ((uint64_t)tab << 32)) >> 32) & ~(S - 1u);
-    return *reinterpret_cast<const Pair<R> *>(smem + off);
+    return lds_at<Pair<R>>(off);
 }
 
-// LDS bytes of the jump queues per lane and path.
-template <typename R, int NOISE> constexpr uint32_t queue_bytes()
+// LDS bytes of the rings per lane and path, with rings of 2^log2 slots.
+template <typename R, int NOISE> __host__ __device__ constexpr uint32_t ring_bytes(uint32_t log2)
 {
-    return (queued_kicks<NOISE>() ? (JCAP + 1) * (uint32_t)sizeof(KickEntry<R>) : 0u) +
-           (((NOISE & NZ_JGRID) != 0) ? jg_cap<R>() * (uint32_t)sizeof(JGKick<R>) : 0u) +
-           (((NOISE & NZ_DICH) != 0) ? (JCAP + 1) * 4u : 0u);
+    return (queued_kicks<NOISE>() ? (uint32_t)sizeof(KickEntry<R>) << log2 : 0u) +
+           (((NOISE & NZ_JGRID) != 0) ? jg_slots<R>() * (uint32_t)sizeof(JGKick<R>) : 0u) +
+           (((NOISE & NZ_DICH) != 0) ? 4u << log2 : 0u);
+}
+// Slots that fit: the busy size while a work-group of `lanes` paths stays within 60 KiB.
+template <typename R, int NOISE> __host__ inline uint32_t ring_fit(uint32_t log2, uint32_t lanes)
+{
+    return ring_bytes<R, NOISE>(log2) * lanes <= 61440u ? log2 : RING_LOG2;
+}
+
+// The smallest of the lanes' values, at most `most`; one lane's value, the same in every
+// lane: kept scalar, so that step numbers and forcing-table reads stay wave-uniform.
+__device__ __forceinline__ uint32_t wave_min(uint32_t v, uint32_t most)
+{
+    for (;;) {
+        const uint64_t b = __ballot(v < most);
+        if (b == 0) return most;
+        most = __builtin_amdgcn_readfirstlane((uint32_t)__shfl(v, __ffsll((long long)b) - 1));
+    }
 }
 
 // ---------------------------------------------------------------------------
 // The integration loop: advances PPL paths per lane over steps [n0, n1) in
-// windows of 2^a.jw_log2 steps (aligned to multiples of it).  Per window the jumps are
-// queued, then the steps run in blocks of 16 sharing one Philox call for
+// blocks of 16 steps (aligned to multiples of 16) sharing one Philox call for
 // Algorithm 2 (4 words x 4 base-6 digits; the normal increments of the
-// non-simplified scheme take one call per 4 steps) and 17 scalar loads of the
+// non-simplified scheme take one call per 4 steps) and 17 loads of the
 // forcing table; x is folded after every step whose index is a multiple of 16.
-// smem holds the jump queues, slot-major with stride qs; column col(j) is this
-// lane's j-th path.  A window ends at a.n_window as well, and snap() runs after that
+// Before a block the rings are filled until they cover it; a lane whose full ring does
+// not cover the block cuts it short for the wave, and the steps it does cover run one by
+// one, as do the ends of a call that are no whole block.
+// LDS holds the rings, slot-major with the lanes' columns side by side, and behind them the
+// waves' increment tables.  A block ends at a.n_window as well, and snap() runs after that
 // step: one launch crosses the start of eq. (31)'s averaging.
 // ---------------------------------------------------------------------------
 template <typename R, int DYN, int POT, int NOISE, int PPL, typename Snap>
 __device__ __forceinline__ void advance_range(const PointConst &a, const uint32_t (&path)[PPL],
                                               Path<R> (&s)[PPL], uint64_t n0, uint64_t n1,
-                                              unsigned char *lds, uint32_t qs, uint32_t col0, Snap snap)
+                                              uint32_t qs, uint32_t col0, Snap snap)
 {
-    const uint32_t dtab = digit_bytes<R, NOISE>() * (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    unsigned char *smem = lds + table_lds<R, NOISE>(blockDim.x >> 6);
+    constexpr bool KICKS = queued_kicks<NOISE>(), JG = (NOISE & NZ_JGRID) != 0, FLIPS = (NOISE & NZ_DICH) != 0;
+    constexpr bool JUMPS = KICKS || JG || FLIPS;
+    const uint32_t slots = 1u << a.ring_log2;
+    Ring kr{0u, qs * (uint32_t)sizeof(KickEntry<R>), slots * qs * (uint32_t)sizeof(KickEntry<R>)};
+    Ring gr{0u, qs * (uint32_t)sizeof(JGKick<R>), jg_slots<R>() * qs * (uint32_t)sizeof(JGKick<R>)};
+    Ring fr{KICKS ? kr.total : (JG ? gr.total : 0u), qs * 4u, slots * qs * 4u};
+    const uint32_t dtab = fr.base + (FLIPS ? fr.total : 0u) +
+                          digit_bytes<R, NOISE>() * (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if constexpr ((NOISE & NZ_GAUSS) != 0) {
         const uint32_t e = threadIdx.x & 63u;
         if (e < 36u)
-            reinterpret_cast<Pair<R> *>(lds + dtab)[e] =
+            lds_at<Pair<R>>(dtab + e * (uint32_t)sizeof(Pair<R>)) =
                 Pair<R>{digit_increment<R>(e / 6u, (R)a.g3), digit_increment<R>(e % 6u, (R)a.g3)};
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
     }
-    KickEntry<R> *kq = reinterpret_cast<KickEntry<R> *>(smem);
-    JGKick<R> *gq = reinterpret_cast<JGKick<R> *>(smem);       // jump-adapted grid (no fixed-grid queue)
-    uint32_t *fq = reinterpret_cast<uint32_t *>(
-        smem + (queued_kicks<NOISE>() ? (JCAP + 1) * qs * sizeof(KickEntry<R>) : 0) +
-        (((NOISE & NZ_JGRID) != 0) ? jg_cap<R>() * qs * sizeof(JGKick<R>) : 0));
     JumpCursor<R> J[PPL];
     const R h = (R)a.dt, hh = (R)(0.5 * a.dt), ngam = (R)(-a.gamma), g3 = (R)a.g3;
     const R kp = pot_factor<POT, R>();
     const R Fa = (R)a.Fa, Fb = (R)a.Fb;
     const uint32_t wave_cols = qs / PPL;
-    auto col = [&](int j) { return (uint32_t)j * wave_cols + col0; };
 
     uint64_t n = n0;
     uint32_t k = (uint32_t)(n % a.spp);           // drive phase of step n
-    if constexpr ((NOISE & NZ_DICH) != 0) {
 #pragma unroll
-        for (int j = 0; j < PPL; ++j) J[j].lev = s[j].d ? Fb : -Fa;
+    for (int j = 0; j < PPL; ++j) {               // empty rings: the next jump is the first not drawn
+        const uint32_t col = (uint32_t)j * wave_cols + col0;
+        if constexpr (KICKS) {
+            J[j].cP = J[j].tP = col * (uint32_t)sizeof(KickEntry<R>);
+            J[j].nP = J[j].uP = (uint32_t)n0 + (uint32_t)s[j].sP;
+            J[j].zP = R(0);
+        }
+        if constexpr (JG) {
+            J[j].cG = J[j].tG = col * (uint32_t)sizeof(JGKick<R>);
+            J[j].poff = (uint32_t)n0 + (uint32_t)s[j].sP;
+            J[j].pth = s[j].thP;
+            J[j].g = JGKick<R>{J[j].poff, R(0), R(0), R(0)};
+        }
+        if constexpr (FLIPS) {
+            J[j].cD = J[j].tD = col * 4u;
+            J[j].nD = J[j].uD = (uint32_t)n0 + (uint32_t)s[j].sD;
+            J[j].dT = s[j].d;
+            J[j].lev = s[j].d ? Fb : -Fa;
+        }
     }
     // Dichotomous noise alone: the wave looks four steps ahead and runs them without a test
     // when none of its lanes flips in them (70% of the time at 1.4e-3 flips per step), and
@@ -459,81 +527,71 @@ __device__ __forceinline__ void advance_range(const PointConst &a, const uint32_
     // step, flips cost every step about 10 of 96 cycles (2^20 paths x 4000 steps: 2.65 ->
     // 2.39 ms).  Poisson kicks come often enough (0.016 per step: some lane of the wave
     // kicks in 98% of all four steps) that looking ahead only costs (2.81 -> 2.83 ms).
-    constexpr bool AHEAD = (NOISE & NZ_DICH) != 0 && (NOISE & NZ_POISSON) == 0;
-    const bool busy = a.jw_log2 <= 8;             // more than 2 flips in 256 steps: some lane in most fours
-    constexpr bool JUMPS = (NOISE & (NZ_POISSON | NZ_DICH)) != 0;
-    if constexpr ((NOISE & NZ_JGRID) != 0) {
-#pragma unroll
-        for (int j = 0; j < PPL; ++j) {           // next kick not yet drawn; empty queue
-            J[j].poff = (uint32_t)s[j].sP;
-            J[j].pth = s[j].thP;
-            J[j].gn = 0;
-        }
-    }
+    constexpr bool AHEAD = FLIPS && (NOISE & NZ_POISSON) == 0;
+    const bool busy = a.ring_log2 > RING_LOG2;    // some lane flips in most fours
 
     while (n < n1) {
-        const uint64_t wnext = ((n >> a.jw_log2) + 1u) << a.jw_log2;
         const uint64_t stop = n < a.n_window && a.n_window < n1 ? a.n_window : n1;
-        uint64_t wend = wnext < stop ? wnext : stop;
-        const uint32_t wdrawn = (uint32_t)(wend - n);   // steps the queues were drawn for
-        uint32_t wlen = wdrawn;
-        uint32_t cover = wdrawn;
-#pragma unroll
-        for (int j = 0; j < PPL; ++j) {
-            if constexpr ((NOISE & NZ_JGRID) != 0) {
-                const uint32_t c = jg_window<R, NOISE>(a, path[j], wlen, s[j].kP, J[j], gq + col(j), qs);
-                cover = c < cover ? c : cover;
-            }
-            if constexpr (queued_kicks<NOISE>()) {
-                const uint32_t c = kick_window<R>(a, path[j], wlen, (uint32_t)s[j].sP, s[j].kP, kq + col(j), qs);
-                cover = c < cover ? c : cover;
-                const KickEntry<R> e = kq[col(j)];
-                J[j].nP = e.off;
-                J[j].zP = e.z;
-                J[j].pP = kq + col(j) + qs;
-            }
-            if constexpr ((NOISE & NZ_DICH) != 0) {
-                const uint32_t c = flip_window<R>(a, path[j], wlen, (uint32_t)s[j].sD, s[j].mD, s[j].d,
-                                                  fq + col(j), qs);
-                cover = c < cover ? c : cover;
-                const uint32_t e = fq[col(j)];
-                J[j].nD = e & ~INLINE_BIT;
-                J[j].cD = qs;
-            }
-        }
-        // A lane whose step holds more kicks than its queue (jump-adapted grid only):
-        // that one step runs alone, drawing the kicks past the queue at the step.
+        const uint32_t n32 = (uint32_t)n;
+        uint32_t run = 16u - (n32 & 15u);
+        if (stop - n < run) run = (uint32_t)(stop - n);
+        // A lane whose step holds more kicks than its ring (jump-adapted grid only): that
+        // one step runs alone, drawing the kicks past the ring at the step.
         bool single = false;
-        if constexpr (queued_kicks<NOISE>() || (NOISE & (NZ_DICH | NZ_JGRID)) != 0) {
-            // A full kick or flip queue ends the window for the wave at the first
-            // jump it does not hold (the minimum over the lanes; on the fixed grid at
-            // least JCAP steps in), rounded down to a 16-step block boundary when one
-            // lies after n.
-            if (__any(cover < wlen)) {
-                uint32_t wl = wlen;
-                for (;;) {
-                    const uint64_t b = __ballot(cover < wl);
-                    if (b == 0) break;
-                    // one lane's value, the same in every lane: keep it scalar, so
-                    // that step counters and forcing-table reads stay wave-uniform
-                    wl = __builtin_amdgcn_readfirstlane((uint32_t)__shfl(cover, __ffsll((long long)b) - 1));
+        if constexpr (JUMPS) {
+            auto cover = [&] {                    // steps from n whose jumps are all queued
+                uint32_t c = 0xFFFFFFFFu;
+#pragma unroll
+                for (int j = 0; j < PPL; ++j) {
+                    if constexpr (KICKS) c = J[j].uP - n32 < c ? J[j].uP - n32 : c;
+                    if constexpr (JG) c = J[j].poff - n32 < c ? J[j].poff - n32 : c;
+                    if constexpr (FLIPS) c = J[j].uD - n32 < c ? J[j].uD - n32 : c;
                 }
-                if constexpr ((NOISE & NZ_JGRID) != 0) {
-                    if (wl == 0) {
-                        single = true;
-                        wl = 1;
+                return c;
+            };
+            if (__builtin_amdgcn_ballot_w64(cover() < run) != 0) {
+                // steps left in the call; at most 2^30, so that the jump after the last one
+                // drawn (a countdown is below 2^31) lies less than 2^32 steps ahead
+                const uint32_t left = n1 - n < 0x40000000u ? (uint32_t)(n1 - n) : 0x40000000u;
+                bool more;
+                do {
+                    more = false;
+#pragma unroll
+                    for (int j = 0; j < PPL; ++j) {
+                        if constexpr (KICKS) more |= draw_kicks<R>(a, path[j], n32, run, left, s[j].kP, J[j], kr);
+                        if constexpr (JG) more |= draw_jg<R, NOISE>(a, path[j], n32, run, left, s[j].kP, J[j], gr);
+                        if constexpr (FLIPS) more |= draw_flips<R>(a, path[j], n32, run, left, s[j].mD, J[j], fr);
+                    }
+                } while (__builtin_amdgcn_ballot_w64(more) != 0);
+                // full rings cut the block short (on the fixed grid not to nothing: the
+                // queued jumps of one lane are at different steps)
+                run = wave_min(cover(), run);
+                if constexpr (JG) {
+                    single = run == 0u;
+                    run = single ? 1u : run;
+                }
+#pragma unroll
+                for (int j = 0; j < PPL; ++j) {   // sentinels, and the current entries again
+                    if constexpr (KICKS) {
+                        lds_at<KickEntry<R>>(J[j].tP) = KickEntry<R>::make(J[j].uP, R(0));
+                        const KickEntry<R> e = lds_at<KickEntry<R>>(J[j].cP);
+                        J[j].nP = e.off;
+                        J[j].zP = e.amplitude();
+                    }
+                    if constexpr (JG) {
+                        lds_at<JGKick<R>>(J[j].tG) = JGKick<R>{J[j].poff, R(0), R(0), R(0)};
+                        J[j].g = lds_at<JGKick<R>>(J[j].cG);
+                    }
+                    if constexpr (FLIPS) {
+                        lds_at<uint32_t>(fr.base + J[j].tD) = J[j].uD;
+                        J[j].nD = lds_at<uint32_t>(fr.base + J[j].cD);
                     }
                 }
-                uint64_t we = n + wl;
-                if (!single && (we & ~(uint64_t)15) > n) we &= ~(uint64_t)15;
-                wend = we;
-                wlen = (uint32_t)(we - n);
             }
         }
-        uint32_t off = 0;
 
-        // Generic single step (block-unaligned window heads and tails); INL: the
-        // single step whose kicks overflow a queue.
+        // Generic single step (ends of a call, blocks cut short); INL: the single step whose
+        // kicks overflow a ring.
         auto one_step = [&](auto inl) {
             constexpr bool INL = decltype(inl)::value;
             const R A0 = drive_at<R>(a, k);
@@ -557,29 +615,23 @@ __device__ __forceinline__ void advance_range(const PointConst &a, const uint32_
                     normal_pair(hi ? q.z : q.x, hi ? q.w : q.y, zc, zs);
                     dxi = g3 * ((n & 1u) ? zs : zc);
                 }
-                full_step<R, DYN, POT, NOISE, INL>(a, path[j], s[j], J[j], gq + col(j), fq + col(j), qs,
-                                                   wlen, off, k,
-                                                   dxi, h, hh, ngam, kp, A0, A1, Fa, Fb);
+                full_step<R, DYN, POT, NOISE, INL>(a, path[j], s[j], J[j], kr, gr, fr, (uint32_t)n, k, dxi, h, hh,
+                                                   ngam, kp, A0, A1, Fa, Fb);
             }
             k = (k + 1u == a.spp) ? 0u : k + 1u;
             ++n;
-            ++off;
             if ((n & 15u) == 0u) {                   // fold at absolute multiples of 16 steps
 #pragma unroll
                 for (int j = 0; j < PPL; ++j) fold<POT, R>(s[j]);
             }
         };
 
-        bool blocks = true;
-        if constexpr ((NOISE & NZ_JGRID) != 0) {
-            if (single) {
-                one_step(std::true_type{});
-                blocks = false;
-            }
-        }
-        while (blocks && n < wend && (n & 15u) != 0u) one_step(std::false_type{});
-
-        while (blocks && n + 16u <= wend) {
+        if (single) {
+            if constexpr (JG) one_step(std::true_type{});
+        } else if (run < 16u) {
+            for (uint32_t t = 0; t < run; ++t) one_step(std::false_type{});
+        } else {
+            uint32_t off = n32;
             U4 q[PPL];
 #pragma unroll
             for (int j = 0; j < PPL; ++j) {
@@ -609,8 +661,8 @@ __device__ __forceinline__ void advance_range(const PointConst &a, const uint32_
 #pragma unroll
                     for (int j = 0; j < PPL; ++j) {
                         const uint32_t u = pick(q[j], (uint32_t)wd);
-                        const Pair<R> p0 = digit_pair<R>(lds, dtab, u);
-                        const Pair<R> p1 = digit_pair<R>(lds, dtab, 36u * u);
+                        const Pair<R> p0 = digit_pair<R>(dtab, u);
+                        const Pair<R> p1 = digit_pair<R>(dtab, 36u * u);
                         dx[j][0] = p0.a;
                         dx[j][1] = p0.b;
                         dx[j][2] = p1.a;
@@ -627,7 +679,7 @@ __device__ __forceinline__ void advance_range(const PointConst &a, const uint32_
                             if constexpr ((NOISE & NZ_GAUSS) != 0) dxi = dx[j][dg];
                             if constexpr ((NOISE & NZ_NORMAL) != 0) dxi = g3 * zn[j][dg];
                             full_step<R, DYN, POT, NOISE, false, decltype(quiet)::value>(
-                                a, path[j], s[j], J[j], gq + col(j), fq + col(j), qs, wlen, off + (uint32_t)dg,
+                                a, path[j], s[j], J[j], kr, gr, fr, off + (uint32_t)dg,
                                 k + (uint32_t)(4 * wd + dg), dxi, h, hh, ngam, kp, A0, A1, Fa, Fb);
                         }
                     }
@@ -635,7 +687,7 @@ __device__ __forceinline__ void advance_range(const PointConst &a, const uint32_
                 if constexpr (AHEAD) {
                     bool jump = false;               // within these four steps
 #pragma unroll
-                    for (int j = 0; j < PPL; ++j) jump = jump || J[j].nD < off + 4u;
+                    for (int j = 0; j < PPL; ++j) jump = jump || J[j].nD - off < 4u;
                     if (busy || __builtin_amdgcn_ballot_w64(jump) != 0) four(std::false_type{});
                     else four(std::true_type{});
                 } else {
@@ -652,36 +704,20 @@ __device__ __forceinline__ void advance_range(const PointConst &a, const uint32_
 #pragma unroll
             for (int j = 0; j < PPL; ++j) fold<POT, R>(s[j]);   // x mod L at the block end
         }
-
-        while (n < wend) one_step(std::false_type{});
-
-        // Countdowns at the window end: the next jump lies at or beyond it.  A window
-        // that ended early gives back the draws of the jumps queued past its end
-        // (fixed grid); on the jump-adapted grid such kicks stay queued for the next.
-        const bool early = wlen < wdrawn;
-#pragma unroll
-        for (int j = 0; j < PPL; ++j) {
-            if constexpr (queued_kicks<NOISE>()) {
-                s[j].sP = (int32_t)(J[j].nP - wlen);
-                if (early)
-                    s[j].kP -= queued_beyond(kq + col(j), qs, wlen, wdrawn,
-                                             [](const KickEntry<R> &e) { return e.off; });
-            }
-            if constexpr ((NOISE & NZ_JGRID) != 0) jg_carry<R>(J[j], gq + col(j), qs, wlen);
-            if constexpr ((NOISE & NZ_DICH) != 0) {
-                s[j].sD = (int32_t)(J[j].nD - wlen);
-                if (early)
-                    s[j].mD -= queued_beyond(fq + col(j), qs, wlen, wdrawn, [](uint32_t e) { return e; });
-            }
-        }
         if (n == a.n_window) snap();
     }
-    if constexpr ((NOISE & NZ_JGRID) != 0) {
-        // every kick drawn lay before the last window's end and has been applied
+    // Countdowns at the end: the next jump is the first one not drawn.
 #pragma unroll
-        for (int j = 0; j < PPL; ++j) {
-            s[j].sP = (int32_t)J[j].poff;
+    for (int j = 0; j < PPL; ++j) {
+        if constexpr (KICKS) {
+            s[j].sP = (int32_t)(J[j].uP - (uint32_t)n);
+        }
+        if constexpr (JG) {
+            s[j].sP = (int32_t)(J[j].poff - (uint32_t)n);
             s[j].thP = J[j].pth;
+        }
+        if constexpr (FLIPS) {
+            s[j].sD = (int32_t)(J[j].uD - (uint32_t)n);
         }
     }
 }
@@ -690,7 +726,7 @@ __device__ __forceinline__ void advance_range(const PointConst &a, const uint32_
 template <typename R, int DYN, int POT, int NOISE, int PPL>
 __global__ void __launch_bounds__(512) k_advance(const KArgs a)
 {
-    extern __shared__ __align__(16) unsigned char smem[];
+    use_dynamic_lds();
     const uint64_t base = (uint64_t)blockIdx.x * PPL * blockDim.x + threadIdx.x;
     if ((base & ~(uint64_t)63) >= a.p.n_paths) return;     // the whole wave
     uint32_t path[PPL];
@@ -704,7 +740,7 @@ __global__ void __launch_bounds__(512) k_advance(const KArgs a)
         path[j] = valid[j] ? (uint32_t)p : a.p.n_paths - 1u;
         load_path<R, POT, NOISE>(a, path[j], s[j]);
     }
-    advance_range<R, DYN, POT, NOISE, PPL>(a.p, path, s, a.n0, a.n1, smem, PPL * blockDim.x, threadIdx.x, [&] {
+    advance_range<R, DYN, POT, NOISE, PPL>(a.p, path, s, a.n0, a.n1, PPL * blockDim.x, threadIdx.x, [&] {
 #pragma unroll
         for (int j = 0; j < PPL; ++j)
             if (valid[j]) { arr<R>(a.xi)[path[j]] = s[j].x; a.wi[path[j]] = s[j].w; }

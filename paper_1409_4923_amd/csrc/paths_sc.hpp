@@ -9,7 +9,7 @@
 // only where the doubled step starts on its own grid, so no step crosses a multiple
 // of dt and the drive at t = (n + u / 2^J) dt is entry (n mod spp) 2^J + u of a table
 // built on the host.  The jump processes keep their dt grid (Algorithms 3 and 4,
-// drawn inline when a countdown runs out: rare, and not worth the window queues of
+// drawn inline when a countdown runs out: rare, and not worth the rings of
 // the fixed-step kernel).
 #pragma once
 

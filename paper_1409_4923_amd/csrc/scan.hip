@@ -114,15 +114,16 @@ bm_tune scan_tune(uint32_t dyn, uint32_t pot, uint32_t noise, uint32_t prec)
     return t;
 }
 
-// LDS of the jump queues of one work-group (see queue_bytes in paths_kernels.hpp).
+// LDS that decides which launch shapes a model takes: per lane and path 10 kicks of the
+// jump-adapted grid (6 in FP64) or 12 kicks, and 12 flips.  The rings of
+// paths_kernels.hpp need at most as much (ring_fit keeps them within 60 KiB).
 size_t queue_lds_bytes(uint32_t noise, uint32_t prec, uint32_t ppl, uint32_t block)
 {
-    const size_t kick = prec == BM_F32 ? sizeof(KickEntry<float>) : sizeof(KickEntry<double>);
+    const bool f32 = prec == BM_F32;
     size_t per = 0;
-    const size_t jg = prec == BM_F32 ? sizeof(JGKick<float>) : sizeof(JGKick<double>);
-    if (noise & BM_NOISE_JUMP_GRID) per += (prec == BM_F32 ? jg_cap<float>() : jg_cap<double>()) * jg;
-    else if (noise & BM_NOISE_POISSON) per += (JCAP + 1) * kick;
-    if (noise & BM_NOISE_DICH) per += (JCAP + 1) * 4;
+    if (noise & BM_NOISE_JUMP_GRID) per += f32 ? 160 : 192;
+    else if (noise & BM_NOISE_POISSON) per += f32 ? 96 : 192;
+    if (noise & BM_NOISE_DICH) per += 48;
     return per * ppl * block;
 }
 
@@ -572,11 +573,13 @@ static int plan_create(const bm_model *models, const bm_run *runs, size_t n, con
     uint64_t chunk_off = 0;
     const uint32_t per_item = 64u * t.paths_per_lane;
     uint64_t n_items = 0;
+    uint32_t ring_log2 = RING_LOG2;
     uint32_t last = 0;
     uint64_t last_phase = 0;
     bool sorted = true;                      // already longest horizon first
     for (size_t i = 0; i < n; ++i) {
         pcs[i] = point_const(&models[i], &runs[i], ws + tab_off);
+        ring_log2 = std::max(ring_log2, pcs[i].ring_log2);
         tab_off += table_entries(&runs[i]) * rs;
         red[i].off = chunk_off;
         red[i].n_chunks = (runs[i].n_paths + 63) / 64;
@@ -626,6 +629,7 @@ static int plan_create(const bm_model *models, const bm_run *runs, size_t n, con
     a.part = (Partial *)(ws + L.part);
     a.counter = (uint32_t *)(ws + L.counter);
     a.n_items = (uint32_t)n_items;
+    a.ring_log2 = ring_log2;
 
     bm_scan_plan *p = new (std::nothrow) bm_scan_plan();
     if (!p) return fail(BM_ERR_INVALID_ARG, "out of host memory");

@@ -33,13 +33,13 @@ struct ScanArgs {
     Partial *part;
     uint32_t *counter;
     uint32_t n_items;
-    uint32_t pad;
+    uint32_t ring_log2;   // slots of the jump rings, the same for all points
 };
 
 template <typename R, int DYN, int POT, int NOISE, int PPL>
 __global__ void __launch_bounds__(512) k_scan(const ScanArgs a)
 {
-    extern __shared__ __align__(16) unsigned char smem[];
+    use_dynamic_lds();
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t qs = PPL * blockDim.x;
     const double L = period<POT>();
@@ -49,7 +49,8 @@ __global__ void __launch_bounds__(512) k_scan(const ScanArgs a)
         it = (uint32_t)__builtin_amdgcn_readfirstlane(__shfl(it, 0, 64));
         if (it >= a.n_items) break;                      // every wave exits here
         const ScanItem item = a.items[it];
-        const PointConst P = a.points[item.point];
+        PointConst P = a.points[item.point];
+        P.ring_log2 = a.ring_log2;
         const uint32_t base = item.chunk * 64u * PPL + lane;
         uint32_t path[PPL];
         bool valid[PPL];
@@ -65,7 +66,7 @@ __global__ void __launch_bounds__(512) k_scan(const ScanArgs a)
             xi[j] = s[j].x;
             wi[j] = s[j].w;
         }
-        advance_range<R, DYN, POT, NOISE, PPL>(P, path, s, 0, P.n_steps, smem, qs, threadIdx.x, [&] {
+        advance_range<R, DYN, POT, NOISE, PPL>(P, path, s, 0, P.n_steps, qs, threadIdx.x, [&] {
 #pragma unroll
             for (int j = 0; j < PPL; ++j) { xi[j] = s[j].x; wi[j] = s[j].w; }
         });

@@ -61,6 +61,27 @@ def test_flips_at_any_rate(rate):
     assert np.max(np.abs(got.x.numpy() - x) / np.maximum(1.0, np.abs(x))) <= 1e-9
 
 
+@pytest.mark.parametrize("extra", [0, W.DICH, W.JUMP_GRID, W.DICH | W.JUMP_GRID],
+                         ids=["kicks", "kicks+flips", "jump-grid", "jump-grid+flips"])
+@pytest.mark.parametrize("rate_dt", [1e-6, 0.016, 0.09, 0.11, 0.6, 3.0])
+def test_kicks_at_any_rate(rate_dt, extra):
+    """Jump rings that are never filled, that wrap, that cut blocks short, of either size,
+    and steps with more kicks than a ring: every kick at its step, against the FP64 oracle;
+    the same bits from one call and from several."""
+    w = W.C2.with_(prec=W.F64, noise=W.GAUSS | W.POISSON | extra, n_paths=130, n_steps=400, n_window=133,
+                   Fa=0.3, Fb=0.6, point=4)
+    rate = rate_dt / w.step()
+    w = w.with_(lam=rate, zeta=0.05 / max(1.0, rate / 5.0), mua=0.5 * rate, mub=rate)
+    say("kicks", rate_dt, extra)
+    one = final(w, [400])
+    got = final(w, [3, 16, 114, 1, 266], B.make_tune(1, 64))
+    assert np.array_equal(one.x.numpy(), got.x.numpy()) and np.array_equal(one.noise.numpy(), got.noise.numpy())
+    x, v, noise, _ = oracle_paths(w, 0, w.n_paths, w.n_steps)
+    assert np.array_equal(got.noise.numpy(), noise)
+    for a, b in ((got.x.numpy(), x), (got.v.numpy(), v)):
+        assert np.max(np.abs(a - b) / np.maximum(1.0, np.abs(b))) <= 1e-9
+
+
 @pytest.mark.parametrize("prec", [W.F32, W.F64], ids=["f32", "f64"])
 @pytest.mark.parametrize("spp", [1, 7, 408, 409, 832, 833, 1500, 3400])
 def test_forcing_tables_of_any_length(spp, prec):

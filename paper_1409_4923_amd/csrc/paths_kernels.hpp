@@ -631,78 +631,80 @@ __device__ __forceinline__ void advance_range(const PointConst &a, const uint32_
         } else if (run < 16u) {
             for (uint32_t t = 0; t < run; ++t) one_step(std::false_type{});
         } else {
-            uint32_t off = n32;
-            U4 q[PPL];
+            do {                                      // without jumps one check covers many blocks
+                uint32_t off = (uint32_t)n;
+                U4 q[PPL];
 #pragma unroll
-            for (int j = 0; j < PPL; ++j) {
-                if constexpr ((NOISE & NZ_GAUSS) != 0)
-                    q[j] = philox4x32_10((uint32_t)(n >> 4), path[j], a.point, TAG_GAUSS, a.key0, a.key1);
-                else
-                    q[j] = U4{0u, 0u, 0u, 0u};
-            }
-            R A[17];                                  // forcing at steps n .. n+16
-            const R *arow = reinterpret_cast<const R *>(a.tab) + k;   // k + 16 < spp + 16
-#pragma unroll
-            for (int t = 0; t < 17; ++t) A[t] = arow[t];
-#pragma unroll
-            for (int wd = 0; wd < 4; ++wd) {
-                R zn[PPL][4];                         // normal increments of steps 4 wd .. 4 wd + 3
-                if constexpr ((NOISE & NZ_NORMAL) != 0) {
-#pragma unroll
-                    for (int j = 0; j < PPL; ++j) {
-                        const U4 qn = philox4x32_10((uint32_t)(n >> 2) + (uint32_t)wd, path[j], a.point,
-                                                    TAG_GAUSS, a.key0, a.key1);
-                        normal_pair(qn.x, qn.y, zn[j][0], zn[j][1]);
-                        normal_pair(qn.z, qn.w, zn[j][2], zn[j][3]);
-                    }
+                for (int j = 0; j < PPL; ++j) {
+                    if constexpr ((NOISE & NZ_GAUSS) != 0)
+                        q[j] = philox4x32_10((uint32_t)(n >> 4), path[j], a.point, TAG_GAUSS, a.key0, a.key1);
+                    else
+                        q[j] = U4{0u, 0u, 0u, 0u};
                 }
-                R dx[PPL][4];                         // three-point increments of the same steps
-                if constexpr ((NOISE & NZ_GAUSS) != 0) {
+                R A[17];                                  // forcing at steps n .. n+16
+                const R *arow = reinterpret_cast<const R *>(a.tab) + k;   // k + 16 < spp + 16
 #pragma unroll
-                    for (int j = 0; j < PPL; ++j) {
-                        const uint32_t u = pick(q[j], (uint32_t)wd);
-                        const Pair<R> p0 = digit_pair<R>(dtab, u);
-                        const Pair<R> p1 = digit_pair<R>(dtab, 36u * u);
-                        dx[j][0] = p0.a;
-                        dx[j][1] = p0.b;
-                        dx[j][2] = p1.a;
-                        dx[j][3] = p1.b;
-                    }
-                }
-                auto four = [&](auto quiet) {
+                for (int t = 0; t < 17; ++t) A[t] = arow[t];
 #pragma unroll
-                    for (int dg = 0; dg < 4; ++dg) {
-                        const R A0 = A[4 * wd + dg], A1 = A[4 * wd + dg + 1];
+                for (int wd = 0; wd < 4; ++wd) {
+                    R zn[PPL][4];                         // normal increments of steps 4 wd .. 4 wd + 3
+                    if constexpr ((NOISE & NZ_NORMAL) != 0) {
 #pragma unroll
                         for (int j = 0; j < PPL; ++j) {
-                            R dxi = R(0);
-                            if constexpr ((NOISE & NZ_GAUSS) != 0) dxi = dx[j][dg];
-                            if constexpr ((NOISE & NZ_NORMAL) != 0) dxi = g3 * zn[j][dg];
-                            full_step<R, DYN, POT, NOISE, false, decltype(quiet)::value>(
-                                a, path[j], s[j], J[j], kr, gr, fr, off + (uint32_t)dg,
-                                k + (uint32_t)(4 * wd + dg), dxi, h, hh, ngam, kp, A0, A1, Fa, Fb);
+                            const U4 qn = philox4x32_10((uint32_t)(n >> 2) + (uint32_t)wd, path[j], a.point,
+                                                        TAG_GAUSS, a.key0, a.key1);
+                            normal_pair(qn.x, qn.y, zn[j][0], zn[j][1]);
+                            normal_pair(qn.z, qn.w, zn[j][2], zn[j][3]);
                         }
                     }
-                };
-                if constexpr (AHEAD) {
-                    bool jump = false;               // within these four steps
+                    R dx[PPL][4];                         // three-point increments of the same steps
+                    if constexpr ((NOISE & NZ_GAUSS) != 0) {
 #pragma unroll
-                    for (int j = 0; j < PPL; ++j) jump = jump || J[j].nD - off < 4u;
-                    if (busy || __builtin_amdgcn_ballot_w64(jump) != 0) four(std::false_type{});
-                    else four(std::true_type{});
-                } else {
-                    four(std::bool_constant<!JUMPS>{});
+                        for (int j = 0; j < PPL; ++j) {
+                            const uint32_t u = pick(q[j], (uint32_t)wd);
+                            const Pair<R> p0 = digit_pair<R>(dtab, u);
+                            const Pair<R> p1 = digit_pair<R>(dtab, 36u * u);
+                            dx[j][0] = p0.a;
+                            dx[j][1] = p0.b;
+                            dx[j][2] = p1.a;
+                            dx[j][3] = p1.b;
+                        }
+                    }
+                    auto four = [&](auto quiet) {
+#pragma unroll
+                        for (int dg = 0; dg < 4; ++dg) {
+                            const R A0 = A[4 * wd + dg], A1 = A[4 * wd + dg + 1];
+#pragma unroll
+                            for (int j = 0; j < PPL; ++j) {
+                                R dxi = R(0);
+                                if constexpr ((NOISE & NZ_GAUSS) != 0) dxi = dx[j][dg];
+                                if constexpr ((NOISE & NZ_NORMAL) != 0) dxi = g3 * zn[j][dg];
+                                full_step<R, DYN, POT, NOISE, false, decltype(quiet)::value>(
+                                    a, path[j], s[j], J[j], kr, gr, fr, off + (uint32_t)dg,
+                                    k + (uint32_t)(4 * wd + dg), dxi, h, hh, ngam, kp, A0, A1, Fa, Fb);
+                            }
+                        }
+                    };
+                    if constexpr (AHEAD) {
+                        bool jump = false;               // within these four steps
+#pragma unroll
+                        for (int j = 0; j < PPL; ++j) jump = jump || J[j].nD - off < 4u;
+                        if (busy || __builtin_amdgcn_ballot_w64(jump) != 0) four(std::false_type{});
+                        else four(std::true_type{});
+                    } else {
+                        four(std::bool_constant<!JUMPS>{});
+                    }
+                    off += 4u;
                 }
-                off += 4u;
-            }
-            n += 16u;
-            k += 16u;
-            if (k >= a.spp) {
-                k -= a.spp;
-                if (k >= a.spp) k %= a.spp;           // periods shorter than a block
-            }
+                n += 16u;
+                k += 16u;
+                if (k >= a.spp) {
+                    k -= a.spp;
+                    if (k >= a.spp) k %= a.spp;           // periods shorter than a block
+                }
 #pragma unroll
-            for (int j = 0; j < PPL; ++j) fold<POT, R>(s[j]);   // x mod L at the block end
+                for (int j = 0; j < PPL; ++j) fold<POT, R>(s[j]);   // x mod L at the block end
+            } while (!JUMPS && n + 16u <= stop);
         }
         if (n == a.n_window) snap();
     }

@@ -326,8 +326,9 @@ int bm_scan_autotune(const bm_model *models, const bm_run *runs, size_t n_points
 
 /* Default launch shape per (dyn, pot, noise, prec) for this process (used when
  * a call gets no bm_tune); the built-in default is 1 path per lane, block 256,
- * groups_per_cu 0, except FP32 inertial models without Poisson or dichotomous
- * noise: 2 paths per lane, block 128 (taken by ensembles of 2^18 paths or more). */
+ * groups_per_cu 0.  For FP32 inertial models without Poisson or dichotomous noise
+ * bm_tune_get_default reports 2 paths per lane, block 128 while none is installed;
+ * ensembles of these models run the built-in shape, scans 1 path per lane, block 64. */
 int bm_tune_set_default(uint32_t dyn, uint32_t pot, uint32_t noise, uint32_t prec, const bm_tune *tune);
 int bm_tune_get_default(uint32_t dyn, uint32_t pot, uint32_t noise, uint32_t prec, bm_tune *out);
 

@@ -416,7 +416,7 @@ static int open_ensemble(const bm_model *model, const bm_run *run, void *d_ws, s
     e->ws = (char *)d_ws;
     e->stream = (hipStream_t)stream;
     e->n_done = steps_done;
-    const bm_tune dt = default_tune(model->dyn, model->pot, model->noise, run->prec, run->n_paths);
+    const bm_tune dt = ensemble_tune(model->dyn, model->pot, model->noise, run->prec);
     e->ppl = dt.paths_per_lane;
     e->block = dt.block;
     fill_kargs(e);
@@ -491,7 +491,7 @@ extern "C" int bm_ensemble_destroy(bm_ensemble *e)
 extern "C" int bm_ensemble_set_tune(bm_ensemble *e, const bm_tune *t)
 {
     if (!e) return fail(BM_ERR_INVALID_ARG, "NULL handle");
-    const bm_tune use = t ? *t : default_tune(e->model.dyn, e->model.pot, e->model.noise, e->run.prec, e->run.n_paths);
+    const bm_tune use = t ? *t : ensemble_tune(e->model.dyn, e->model.pot, e->model.noise, e->run.prec);
     // the step-control kernel draws its jumps inline: no LDS queues to fit
     const uint32_t queued = step_control(&e->run) ? (e->model.noise & BM_NOISE_GAUSS) : e->model.noise;
     int rc = check_tune(&use, queued, e->run.prec);

@@ -27,7 +27,8 @@ int check_device(int *dev_out);                     // a gfx950 device is curren
 // Launch shape used when the caller passes no bm_tune: set by bm_tune_set_default
 // (or bm_scan_autotune), else the built-in shape of the model, for an ensemble of
 // n_paths (default: many).
-bm_tune default_tune(uint32_t dyn, uint32_t pot, uint32_t noise, uint32_t prec, uint64_t n_paths = ~0ull);
+bm_tune default_tune(uint32_t dyn, uint32_t pot, uint32_t noise, uint32_t prec);
+bm_tune ensemble_tune(uint32_t dyn, uint32_t pot, uint32_t noise, uint32_t prec);
 size_t queue_lds_bytes(uint32_t noise, uint32_t prec, uint32_t ppl, uint32_t block);
 int check_tune(const bm_tune *t, uint32_t noise, uint32_t prec);
 

@@ -73,25 +73,42 @@ bm_tune builtin_tune()
 namespace bm {
 namespace host {
 
-bm_tune default_tune(uint32_t dyn, uint32_t pot, uint32_t noise, uint32_t prec, uint64_t n_paths)
+namespace {
+bool installed_tune(uint32_t dyn, uint32_t pot, uint32_t noise, uint32_t prec, bm_tune *t)
 {
-    {
-        std::lock_guard<std::mutex> lk(g_tune_mu);
-        auto it = g_tune.find(std::make_tuple(dyn, pot, noise, prec));
-        if (it != g_tune.end()) return it->second.t;
-    }
+    std::lock_guard<std::mutex> lk(g_tune_mu);
+    auto it = g_tune.find(std::make_tuple(dyn, pot, noise, prec));
+    if (it == g_tune.end()) return false;
+    *t = it->second.t;
+    return true;
+}
+bool f32_inertial_no_jumps(uint32_t dyn, uint32_t noise, uint32_t prec)
+{
+    return prec == BM_F32 && dyn == BM_INERTIAL && (noise & (BM_NOISE_POISSON | BM_NOISE_DICH)) == 0;
+}
+} // namespace
+
+// The shape bm_tune_get_default and bm_tune_lookup report.
+bm_tune default_tune(uint32_t dyn, uint32_t pot, uint32_t noise, uint32_t prec)
+{
     bm_tune t = builtin_tune();
-    // FP32 inertial paths without jump processes: two paths per lane give the step
-    // loop independent work to interleave once every SIMD has waves to choose from
-    // (179 against 187 ns per step at 2^18 paths, four waves per SIMD); with fewer a step
-    // lasts as long as one wave's instructions, and a second path doubles them (105
-    // against 59 ns up to 2^16 paths, 181 against 110 at 2^17).  With jump queues the
-    // second path costs occupancy instead.
-    if (prec == BM_F32 && dyn == BM_INERTIAL && (noise & (BM_NOISE_POISSON | BM_NOISE_DICH)) == 0 &&
-        n_paths >= (1u << 18)) {
+    if (!installed_tune(dyn, pot, noise, prec, &t) && f32_inertial_no_jumps(dyn, noise, prec)) {
         t.paths_per_lane = 2;
         t.block = 128;
     }
+    return t;
+}
+
+// Launch shape of an ensemble without a bm_tune: the installed one, else one path per lane
+// and 256 lanes at any size.  A second path per lane gives a wave independent work to
+// interleave, but eight waves per SIMD do as well (FP32 inertial Gaussian, 2^20 paths: 633
+// ns per step against 650 with two paths in 128 lanes; 2^18: 175 against 177; normal
+// increments 998 against 1060), and where the waves are few it doubles their length
+// (20000 paths: 56 against 101 ns).  With jump rings it costs occupancy.
+bm_tune ensemble_tune(uint32_t dyn, uint32_t pot, uint32_t noise, uint32_t prec)
+{
+    bm_tune t = builtin_tune();
+    installed_tune(dyn, pot, noise, prec, &t);
     return t;
 }
 
@@ -99,18 +116,13 @@ bm_tune default_tune(uint32_t dyn, uint32_t pot, uint32_t noise, uint32_t prec, 
 // A scan ends with its longest horizons, whose waves run the slower the more paths they
 // carry (512 points of up to 10^4 steps: 3.86 against 4.15 ms with two; 64 points: 0.82
 // against 1.11 ms), and one path per lane fills the chip as well as two (20000 points of
-// 2000 steps: 6.59 against 6.61 ms).  FP32 inertial models without jump queues run in
+// 2000 steps: 6.59 against 6.61 ms).  FP32 inertial models without jump rings run in
 // groups of one wave, which spread evenly over the CUs (64 points: 0.82 against 0.92 ms
 // with 256 lanes); the others measured no better so (FP64: 0.89 against 0.81 ms).
 bm_tune scan_tune(uint32_t dyn, uint32_t pot, uint32_t noise, uint32_t prec)
 {
-    {
-        std::lock_guard<std::mutex> lk(g_tune_mu);
-        auto it = g_tune.find(std::make_tuple(dyn, pot, noise, prec));
-        if (it != g_tune.end()) return it->second.t;
-    }
     bm_tune t = builtin_tune();
-    if (prec == BM_F32 && dyn == BM_INERTIAL && (noise & (BM_NOISE_POISSON | BM_NOISE_DICH)) == 0) t.block = 64;
+    if (!installed_tune(dyn, pot, noise, prec, &t) && f32_inertial_no_jumps(dyn, noise, prec)) t.block = 64;
     return t;
 }
 

@@ -194,10 +194,10 @@ template <int POT, typename R> __device__ __forceinline__ void fold(Path<R> &s)
 // with room draws along, so the draws of many blocks happen side by side whichever lane
 // asked for them.  (Windows of a fixed number of steps, whose draws took as many turns as
 // the lane with the most jumps needed, took 1.6 times the turns at 0.016 kicks per step.)
-// Windows -> rings, 4000 steps: 500001 paths on the jump-adapted grid 3.60 -> 3.40 ms,
+// Windows -> rings, 4000 steps: 500001 paths on the jump-adapted grid 3.60 -> 3.36 ms,
 // 262147 FP64 paths with kicks 558 -> 533 us per 800 steps (rings of 24 KiB per 256 lanes
 // instead of queues of 48: four groups per CU, as the registers allow, instead of three), 2^20 inertial Poisson
-// paths 2.80 -> 2.75 ms.
+// paths 2.80 -> 2.74 ms.
 // A ring holds one jump less than its slots: the slot behind the last queued jump is a
 // sentinel with the step of the first jump not drawn yet.
 // ---------------------------------------------------------------------------
@@ -213,10 +213,10 @@ template <typename R> struct alignas(4 * sizeof(R)) JGKick {
     uint32_t off;
     R th, z, u;
 };
-// Slots of its ring: 8 in FP32, 6 in FP64, so that the FP64 rings of 256 lanes with the
-// dichotomous ring still fit in 64 KiB of LDS.  A step with more kicks draws the rest at
-// the step.
-template <typename R> constexpr uint32_t jg_slots() { return sizeof(R) == 4 ? 8u : 6u; }
+// Slots of its ring: 9 in FP32, the most that four groups of 256 lanes hold in a CU's
+// LDS; 6 in FP64, so that the FP64 rings of 256 lanes with the dichotomous ring still fit
+// in 64 KiB.  A step with more kicks draws the rest at the step.
+template <typename R> constexpr uint32_t jg_slots() { return sizeof(R) == 4 ? 9u : 6u; }
 
 // A queued kick: its step and amplitude (FP64: 12 bytes, so that LDS does not limit the
 // groups of a CU).
@@ -260,7 +260,7 @@ struct Ring {
 };
 template <typename E> inline constexpr bool ring_masked = true; // 2^k slots of 2^i bytes, 2^j columns
 template <> inline constexpr bool ring_masked<KickEntry<double>> = false;
-template <> inline constexpr bool ring_masked<JGKick<double>> = false;
+template <typename R> inline constexpr bool ring_masked<JGKick<R>> = false;
 template <typename E> __device__ __forceinline__ uint32_t ring_next(const Ring &r, uint32_t at)
 {
     const uint32_t n = at + r.stride;

@@ -35,15 +35,15 @@ FP32_PEAK_FLOPS = 157.3e12                                   # packed FP32 vecto
 FP64_PEAK_FLOPS = 78.6e12
 
 # HBM traffic of k_advance on the default workload from two rocprofv3 --pmc runs
-# (FETCH_SIZE, then WRITE_SIZE), averaged over the two launches of one step and
+# (FETCH_SIZE, then WRITE_SIZE; one launch per step, averaged over two steps),
 # scaled by what the same counters read for a 1 GiB device copy (FETCH_SIZE
 # reads 0.5 GiB for it: factor 2.0; WRITE_SIZE reads 1 GiB: factor 1.0).  Valid
 # only while the integration kernel's sources hash to KERNEL_SOURCES_SHA256.
 TRAFFIC_WORKLOAD = "inertial-poisson-f32-2^20"
-TRAFFIC_BYTES_PER_LAUNCH = ((10528.0625 + 10335.0) / 2 * 2.0 + (28672.0 + 20480.0) / 2 * 1.0) * 1024
+TRAFFIC_BYTES_PER_LAUNCH = ((10480.75 + 10323.0) / 2 * 2.0 + 28672.0 * 1.0) * 1024
 KERNEL_SOURCES = ("common.hpp", "paths.hpp", "paths_kernels.hpp", "paths_tu.inc", "paths_f32_in.hip",
                   "launch.hpp")
-KERNEL_SOURCES_SHA256 = "d6fbeecabe7d6e2b68fcf7361058bc72e5508394e0aa8650ead8592aa18b704f"
+KERNEL_SOURCES_SHA256 = "e99936ab2d55e0a85eb395591d5f0d22a57ac3eae5ee36abc7877f805965be56"
 
 
 def algorithmic_work(w):
@@ -57,14 +57,15 @@ def algorithmic_work(w):
       Algorithm 1: inertial 8 FMA + 1 add, overdamped 4 FMA + 1 add (the noise
         increment is added once, and the predictor's and corrector's trapezoids
         share the base y + F1 dt/2), + 1 add for a kick;
-      dichotomous level: 1 select + 2 adds; fold: 4 ops per 16 steps;
-      Algorithm 2 (three-point): 2 compares + 2 selects + 2 shifts for the next
-        base-6 digit + Philox4x32-10 (10 rounds x (2 wide products + 2 three-way
+      dichotomous level: 2 adds (the level changes only at a flip); fold: 4 ops per 16
+        steps;
+      Algorithm 2 (three-point): from a table of digit pairs, a multiply and a mask per
+        2 steps and a multiply per 4 + Philox4x32-10 (10 rounds x (2 wide products + 2 three-way
         xors) = 40 ops) per 16 steps;  normal increments: Philox per 4 steps,
         Box-Muller (8 ops + log, sqrt, cos, sin per pair) and the scale;
       Algorithm 3: 1 compare per step; per kick half a Philox block (20), the FP32
         countdown (8), the amplitude (4 + log), queue write and read (4);
-      Algorithm 4: 1 compare per step; per flip a quarter block (10), countdown (8 +
+      Algorithm 4: 1 compare per step with kicks, else per 4 steps; per flip a quarter block (10), countdown (8 +
         log), state flip (1), queue write and read (3).
     The jump-adapted grid adds, per kick, a Philox block for the piece increment (40 /
     16 or 40 / 4), the FP64 kick time (log, divide: ~30), the drive inside the step
@@ -96,7 +97,7 @@ def algorithmic_work(w):
     ops += 4.0 / 16.0
     flops += 2.0 / 16.0
     if w.noise & W.GAUSS:
-        ops += 6 + 40.0 / 16.0
+        ops += 1.25 + 40.0 / 16.0
     if w.noise & W.NORMAL:
         ops += 40.0 / 4.0 + 4 + 1
         trans += 2
@@ -114,7 +115,7 @@ def algorithmic_work(w):
             flops += p_kick * (20 + (17 if inertial else 9) + 3 * e_fl)
     if w.noise & W.DICH:
         p_flip = max(-math.expm1(-w.mua * h), -math.expm1(-w.mub * h))
-        ops += 3 + 1 + p_flip * (10 + 8 + 1 + 3)
+        ops += 2 + (1.0 if kick else 0.25) + p_flip * (10 + 8 + 1 + 3)
         trans += p_flip
         flops += 2 + p_flip
     return ops, trans, flops
@@ -250,15 +251,14 @@ def roofline_of(w, int_s: float):
     from paper_1409_4923_amd import workloads as W
     ops, trans, flops = algorithmic_work(w)
     ps = w.path_steps()
-    launches = 2 if 0 < w.n_window < w.n_steps else 1
     peak_flops = FP32_PEAK_FLOPS if w.prec == W.F32 else FP64_PEAK_FLOPS
     achieved = ops * ps / int_s
     return {"bound": "alu", "kernel": "k_advance (integration loop)",
             "achieved": achieved / 1e12, "peak": VALU_LANE_OPS_PEAK / 1e12, "unit": "TOP/s (VALU lane-ops)",
             "frac": achieved / VALU_LANE_OPS_PEAK, "traffic": None,
             "ops_per_path_step": ops, "trans_ops_per_path_step": trans,
-            "path_steps_per_launch": ps / launches, "kernel_ms_per_launch": int_s * 1e3 / launches,
-            "launches_per_step": launches,
+            "path_steps_per_launch": ps, "kernel_ms_per_launch": int_s * 1e3,
+            "launches_per_step": 1,
             "fp32_flops" if w.prec == W.F32 else "fp64_flops": {
                 "flops_per_path_step": flops, "achieved_tflops": flops * ps / int_s / 1e12,
                 "peak_tflops": peak_flops / 1e12, "frac": flops * ps / int_s / peak_flops}}

@@ -196,12 +196,12 @@ __global__ void __launch_bounds__(256) k_compact(const float *stdv, uint64_t B, 
 size_t up(size_t v) { return (v + 255) & ~(size_t)255; }
 
 struct MlpLayout {
-    size_t a1, a2, dz2, dz3, hpart, cpart, y, blk, total;
+    size_t a1, a2, dz1, dz2, dz3, u, hpart, y, blk, total;
 };
 
 // Work-groups per member of the training pass: one per 32 rows, but no more in all than
 // the 256 CUs take at once (a group then takes several row tiles, in as many passes as the
-// fullest group needs), so the partials to add stay few at any batch.
+// fullest group needs).
 int train_groups(uint32_t nm, uint64_t batch)
 {
     const int tiles = (int)(batch / TR);
@@ -216,14 +216,14 @@ MlpLayout mlp_layout(uint32_t nm, uint64_t batch, bool training)
     const uint64_t R = batch;
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t at = o; o += up(bytes); return at; };
-    if (training) {                    // operands of the weight gradients, partials
+    if (training) {                    // operands of the gradients, records of the output layer
         L.a1 = take(nm * R * H * 2);
         L.a2 = take(nm * R * H * 2);
+        L.dz1 = take(nm * R * H * 2);
         L.dz2 = take(nm * R * H * 2);
         L.dz3 = take(nm * R * H * 2);
-        const size_t parts = (size_t)nm * train_groups(nm, batch);
-        L.hpart = take(parts * HEAD_W * 4);
-        L.cpart = take(parts * NV1 * H * 4);
+        L.u = take(nm * R * IN * 4);
+        L.hpart = take(nm * (R / HEAD_ROWS) * HEAD_W * 4);
     } else {                           // inference keeps its activations in registers
         L.y = take(nm * batch * 4);
         L.blk = take(((batch + 255) / 256) * 4 + 4);
@@ -717,16 +717,23 @@ extern "C" int bm_mlp_backward(uint32_t n_members, const float *d_params, const 
     a.B = (int)batch;
     a.a1T = (bf16_t *)(ws + L.a1);
     a.a2T = (bf16_t *)(ws + L.a2);
+    a.dz1T = (bf16_t *)(ws + L.dz1);
     a.dz2T = (bf16_t *)(ws + L.dz2);
     a.dz3T = (bf16_t *)(ws + L.dz3);
+    a.u = (float *)(ws + L.u);
     a.hpart = (float *)(ws + L.hpart);
-    a.cpart = (float *)(ws + L.cpart);
     a.members = (int)n_members;
     a.groups = train_groups(n_members, batch);
     a.grad = d_grad;
     a.loss = d_loss;
     hipLaunchKernelGGL(k_train_rows, dim3((uint32_t)a.groups, n_members), dim3(TBT), 0, s, a);
-    hipLaunchKernelGGL(k_train_wgrad, dim3(WG_BLOCKS * n_members), dim3(TBT), 0, s, a);
+    const dim3 grid(WG_BLOCKS * n_members);
+    switch (wgrad_split((int)batch)) {
+    case 1: hipLaunchKernelGGL(k_train_wgrad<1>, grid, dim3(TBT), 0, s, a); break;
+    case 2: hipLaunchKernelGGL(k_train_wgrad<2>, grid, dim3(TBT), 0, s, a); break;
+    case 4: hipLaunchKernelGGL(k_train_wgrad<4>, grid, dim3(TBT), 0, s, a); break;
+    default: hipLaunchKernelGGL(k_train_wgrad<8>, grid, dim3(TBT), 0, s, a); break;
+    }
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? ok() : hip_fail(e, "bm_mlp_backward");
 }

@@ -7,14 +7,19 @@
 // lane's registers, so that k_train_wgrad loads a fragment as 1 KiB in a row (stored
 // [feature][row] instead, the 16 rows of a fragment lie a power of two apart in the same
 // few L2 channels: 16.6 us at 1024 rows), and per-group partial
-// sums of the small layers' gradients.  k_train_wgrad forms dW2, dW3 and their biases and
-// adds those partials.
+// sums of the output layer's gradients.  k_train_wgrad forms dW2, dW3, their biases and
+// the input layer's gradients, and adds those partials.
+//
+// Every gradient is a sum over the batch in one order that depends on the batch alone (the
+// order of a layer-by-layer step: chunks of rows summed in ascending order, the chunks
+// added one after another), so a seeded training run repeats bit for bit whatever the
+// launch.  The rules are wgrad_split, bias_tile, HEAD_ROWS and column_rows below.
 //
 // What bounds a step of this size (5 members x 1024 rows: 4 GFLOP, 18 MB) is latency:
 // one launch per layer and direction (13 of them, each 4 - 17 us, with z, a and dz in
-// memory between them) took 97 us with the Adam step, 197 us at 4096 rows; the two
-// launches take 27 + 10.5 us and 72 + 24 us, 40 and 98 us with the Adam step.  The arithmetic per element is the layer-by-layer one in the same order up to dz1, so
-// the BF16 roundings between the layers are the same.
+// memory between them) took 97.6 us with the Adam step, 195.6 us at 4096 rows; the two
+// launches take 25 + 10 us and 66 + 25 us, 36.7 and 90.2 us with the Adam step.  The
+// arithmetic and the roundings are the layer-by-layer ones, bit for bit.
 #pragma once
 
 #include "mlp_kernels.hpp"
@@ -27,8 +32,24 @@ constexpr int TWAVES = 8, TBT = 64 * TWAVES;
 constexpr int TLD = H + 8;              // LDS row of activations (bf16): 4 banks further per row
 constexpr int TTL = 32 + 4;             // LDS row of a wave's transposed weight slice: 8 banks further per 4 rows
 constexpr int HEAD_W = H + 2;           // partial record of the output layer: dW4[256], db4, sum e^2
-constexpr int NV1 = IN + 1;             // of the input layer: dW1[o][0..4], db1[o]
+constexpr int HEAD_ROWS = 16;           // rows of a record: four sums of four rows, added in order
+constexpr int NV1 = IN + 1;             // sums of the input layer: dW1[o][0..4], db1[o]
 static_assert(TWAVES * 32 == H, "a wave owns 32 features of a layer");
+
+// Chunks of rows whose products with the 256 x 256 weight gradients are summed apart: the
+// largest power of two <= min(8, B / 256) with B / split a multiple of 32.
+__host__ __device__ constexpr int wgrad_split(int B)
+{
+    int ks = 1;
+    while (ks < 8 && 2 * ks * 256 <= B && B % (2 * ks * 32) == 0) ks *= 2;
+    return ks;
+}
+// The bias gradient of a chunk is four sums: of the q-th quarters of its tiles of this
+// many rows.
+__host__ __device__ constexpr int bias_tile(int chunk) { return chunk % 128 == 0 ? 128 : 32; }
+// Rows of a partial sum of the input layer's gradients.
+__host__ __device__ constexpr int column_rows(int B) { return B / 64 < 16 ? 16 : B / 64; }
+constexpr int MAX_COLUMNS = 64;         // most partial sums: B / column_rows(B)
 
 struct TrainArgs {
     const float *x, *t;                 // rows [.][5] and targets
@@ -36,8 +57,9 @@ struct TrainArgs {
     const bf16_t *wbf;
     const float *params;
     int B;                              // rows per member, a multiple of 64
-    bf16_t *a1T, *a2T, *dz2T, *dz3T;    // [member][B / 32][16 feature tiles][64 lanes][8 rows]
-    float *hpart, *cpart;               // [member][group][HEAD_W], [member][group][NV1][H]
+    bf16_t *a1T, *a2T, *dz1T, *dz2T, *dz3T;   // [member][B / 32][16 feature tiles][64 lanes][8 rows]
+    float *u;                           // normalised inputs [member][B][IN]
+    float *hpart;                       // [member][B / HEAD_ROWS][HEAD_W]
     int members;
     int groups;                         // work-groups per member (gridDim.x of k_train_rows)
     float *grad, *loss;
@@ -108,10 +130,6 @@ __global__ void __launch_bounds__(TBT, 2) k_train_rows(const TrainArgs a)
     };
     int tile = blockIdx.x;
     fetch(tile);
-    float sw = 0.0f, sb = 0.0f, se = 0.0f;      // dW4 (threads < 256), db4 and sum e^2 (lanes of wave 4)
-    float s1[NV1];                              // dW1, db1 (threads >= 256)
-#pragma unroll
-    for (int q = 0; q < NV1; ++q) s1[q] = 0.0f;
 
     for (; tile < B / TR; tile += a.groups) {
         // The lane and a zero offset, opaque per tile: addresses are formed where they are
@@ -212,7 +230,10 @@ __global__ void __launch_bounds__(TBT, 2) k_train_rows(const TrainArgs a)
             float u[IN];
             normalise(xr, u);
 #pragma unroll
-            for (int j = 0; j < IN; ++j) sU[tid][j] = u[j];
+            for (int j = 0; j < IN; ++j) {
+                sU[tid][j] = u[j];
+                a.u[((uint64_t)m * B + tile * TR + tid) * IN + j] = u[j];
+            }
             sTgt[tid] = tr;
         }
         fetch(tile + a.groups);
@@ -316,193 +337,323 @@ __global__ void __launch_bounds__(TBT, 2) k_train_rows(const TrainArgs a)
                 store(rt, t, v, a.dz3T);
             }
         }
+        float *rec = a.hpart + ((uint64_t)m * (B / HEAD_ROWS) + tile * (TR / HEAD_ROWS)) * HEAD_W;
         if (tid < H) {
-#pragma unroll 8
-            for (int r = 0; r < TR; ++r) sw = fmaf(sDy[r], bf2f(sAct[0][r * TLD + tid]), sw);
-        } else if (tid < H + TR) {              // a row per lane, the lanes added at the end
-            sb += sDy[tid - H];
-            se = fmaf(sE[tid - H], sE[tid - H], se);
+#pragma unroll
+            for (int q = 0; q < TR / HEAD_ROWS; ++q) {
+                float sw[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    sw[k] = 0.0f;
+#pragma unroll
+                    for (int rr = 0; rr < 4; ++rr) {
+                        const int r = HEAD_ROWS * q + 4 * k + rr;
+                        sw[k] = fmaf(sDy[r], bf2f(sAct[0][r * TLD + tid]), sw[k]);
+                    }
+                }
+                rec[q * HEAD_W + tid] = ((sw[0] + sw[1]) + sw[2]) + sw[3];
+            }
+        } else if (tid < H + TR / 4) {          // four rows per lane
+            const int r0 = 4 * (tid - H);
+            float sb = 0.0f, se = 0.0f;
+#pragma unroll
+            for (int rr = 0; rr < 4; ++rr) {
+                sb += sDy[r0 + rr];
+                se = fmaf(sE[r0 + rr], sE[r0 + rr], se);
+            }
+            float b[4], e[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                b[k] = __shfl(sb, (lane & ~3) + k, 64);
+                e[k] = __shfl(se, (lane & ~3) + k, 64);
+            }
+            if ((lane & 3) == 0) {
+                rec[lane / 4 * HEAD_W + H] = ((b[0] + b[1]) + b[2]) + b[3];
+                rec[lane / 4 * HEAD_W + H + 1] = ((e[0] + e[1]) + e[2]) + e[3];
+            }
         }
         __syncthreads();
         // ---- dz2 and dz1 ----
         backward(sAct[1], wt, acc);
         asm volatile("" ::: "memory");
         load_wt(BOFF_W2, wt);
-        auto gradient = [&](int rt, int t, const float (&z)[4], bf16_t *dst) {
+        auto gradient = [&](int rt, int t, const float (&z)[4]) {
             bf16x4 v;
 #pragma unroll
             for (int e = 0; e < 4; ++e) v[e] = (__bf16)(acc[rt][t][e] * gelu_grad(z[e]));
-            put(rt, t, v, dst);
             return v;
         };
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
-            for (int rt = 0; rt < TRT; ++rt) store(rt, t, gradient(rt, t, z2[rt][t], sAct[0]), a.dz2T);
+            for (int rt = 0; rt < TRT; ++rt) {
+                const bf16x4 v = gradient(rt, t, z2[rt][t]);
+                put(rt, t, v, sAct[0]);
+                store(rt, t, v, a.dz2T);
+            }
         __syncthreads();
         backward(sAct[0], wt, acc);
-        input_layer([&](int rt, int t, const float (&z)[4]) { gradient(rt, t, z, sAct[1]); });
-        __syncthreads();
-        if (tid >= H) {
-            const int o = tid - H;
-#pragma unroll 4
-            for (int r = 0; r < TR; ++r) {
-                const float d = bf2f(sAct[1][r * TLD + o]);
-#pragma unroll
-                for (int j = 0; j < IN; ++j) s1[j] = fmaf(d, sU[r][j], s1[j]);
-                s1[IN] += d;
-            }
-        }
+        input_layer([&](int rt, int t, const float (&z)[4]) { store(rt, t, gradient(rt, t, z), a.dz1T); });
         __syncthreads();                        // the next tile overwrites sU and sAct
-    }
-    if (tid >> 6 == H / 64) {
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) {
-            sb += __shfl_xor(sb, off, 64);
-            se += __shfl_xor(se, off, 64);
-        }
-    }
-    const uint64_t blk = (uint64_t)m * a.groups + blockIdx.x;
-    if (tid < H) {
-        a.hpart[blk * HEAD_W + tid] = sw;
-    } else {
-        if (tid == H) {
-            a.hpart[blk * HEAD_W + H] = sb;
-            a.hpart[blk * HEAD_W + H + 1] = se;
-        }
-#pragma unroll
-        for (int q = 0; q < NV1; ++q) a.cpart[(blk * NV1 + q) * H + tid - H] = s1[q];
     }
 }
 
 // Weight gradients dW[o][i] = sum_r dz[r][o] a[r][i] of the 256 x 256 layers from the
-// fragments of k_train_rows: grid (64 + NV1 + 1) members; a group of the first 64 members
-// forms a 32 x 64 tile.  The rows are dealt to the eight waves in
-// slices of 32 (wave w: slices w, w + 8, ...), up to four slices' loads in flight, and the
-// waves' sums are added in a fixed order through LDS: splitting the rows inside the group
-// keeps the chip's 256 CUs busy at small batches without partials in memory.  The bias
-// gradients are the row sums of the dz fragments of the first column tile.  The last
-// (NV1 + 1) members blocks add the groups' partials of the input and the output layer in order.
+// fragments of k_train_rows, KS = wgrad_split(B): grid (64 + COLUMN_BLOCKS + 1) members; a
+// group of the first 64 members forms a 32 x 64 tile.  Its eight waves share the KS chunks
+// of rows, 8 / KS waves to a chunk with KS of the tile's eight 16 x 16 products each, so
+// that a product is one accumulation over its chunk and all waves work at any batch; up to
+// SL slices of 32 rows have their loads in flight.  The chunks are added in order through
+// LDS, which needs no partials in memory.  The bias gradients are row sums of dz in the
+// groups of the first column tile.  The last (COLUMN_BLOCKS + 1) members blocks form the
+// gradients of the input layer and add the records of the output layer.
+// 9.8 us at 1024 rows and 24.9 us at 4096; slices dealt to the waves in turn (a quarter
+// fewer loads at KS = 4, but sums in another order) took 10.4 and 24.0 us.
 constexpr int WG_TILES = 64;
-constexpr int WG_BLOCKS = WG_TILES + NV1 + 1;   // per member
+constexpr int CW = 16;                          // columns of the input layer per block
+constexpr int COLUMN_BLOCKS = H / CW;
+constexpr int WG_BLOCKS = WG_TILES + COLUMN_BLOCKS + 1;   // per member
 constexpr int WGM = 32, WGN = 64;
 
-__global__ void __launch_bounds__(TBT, 2) k_train_wgrad(const TrainArgs a)
+// The value of lane I of this lane's row of 16.
+template <int I> __device__ __forceinline__ float row_lane(float v)
 {
-    __shared__ __align__(16) float red[TWAVES / 2][WGM * WGN];
-    __shared__ float redb[TWAVES][WGM];
+    return __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(v), 0x150 + I, 0xF, 0xF, true));
+}
+
+// 16 rows of dz1 in one column, and of the inputs: one row per lane of a row of lanes.
+struct ColumnRows {
+    bf16x8 d[2];
+    float u[IN];
+};
+
+// Adds rows I .. 15 of `v` to the sums of the lane's column: those below n (the same in all
+// lanes); with EDGES those from `first` on, n of them, as zeros elsewhere.
+template <int I, bool EDGES>
+__device__ __forceinline__ void add_rows(const ColumnRows &v, int first, int n, float (&s)[NV1])
+{
+    if constexpr (I < 16) {
+        if (EDGES || I < n) {
+            float d = (float)v.d[I >> 3][I & 7];
+            if constexpr (EDGES) d = (uint32_t)(I - first) < (uint32_t)n ? d : 0.0f;
+#pragma unroll
+            for (int j = 0; j < IN; ++j) s[j] = fmaf(d, row_lane<I>(v.u[j]), s[j]);
+            s[IN] += d;
+        }
+        add_rows<I + 1, EDGES>(v, first, n, s);
+    }
+}
+
+// dW1[o][0..4] and db1[o] of 16 columns o: a partial sum over column_rows(B) rows per row
+// of 16 lanes, a column per lane, then the partial sums in order.  16 batch rows at a time:
+// lane i holds the inputs of row i, which reach the other lanes of its row by DPP (read by
+// every lane for itself, from memory or LDS, the inputs are ten times dz's bytes).  Whole
+// waves on one partial sum and 64 columns left 20 blocks of 5 members to work for 22 us at
+// 1024 rows; these 80 end before the tiles do.
+__device__ __forceinline__ void column_sums(const TrainArgs &a, int m, int f0, float (*part)[NV1][CW])
+{
+    const int tid = threadIdx.x, c = tid & 15;
+    const int B = a.B, rows = column_rows(B), n = B / rows;
+    const bf16_t *dz = a.dz1T + (uint64_t)m * H * B + (uint64_t)(f0 / 16) * 512 + c * 8;
+    const float *um = a.u + (uint64_t)m * B * IN;
+    auto eight = [&](int r) { return dz + (uint64_t)(r >> 5) * (32 * H) + ((r >> 3) & 3) * 128; };
+    // rows r .. r + 15, r a multiple of 8; those from `end` on are not used
+    auto load = [&](int r, int end) {
+        ColumnRows v;
+        v.d[0] = *reinterpret_cast<const bf16x8 *>(eight(r < end ? r : 0));
+        v.d[1] = *reinterpret_cast<const bf16x8 *>(eight(r + 8 < end ? r + 8 : 0));
+        const float *u = um + (uint64_t)(r + c < end ? r + c : 0) * IN;
+#pragma unroll
+        for (int j = 0; j < IN; ++j) v.u[j] = u[j];
+        return v;
+    };
+    const bool aligned = rows % 8 == 0;             // else a partial sum may begin inside an eight
+    for (int k = tid >> 4; k < n; k += TBT / 16) {
+        const int lo = k * rows, hi = lo + rows, at = lo & ~7;
+        const int span = aligned ? rows : rows + 7;
+        float s[NV1];
+#pragma unroll
+        for (int q = 0; q < NV1; ++q) s[q] = 0.0f;
+        ColumnRows v = load(at, hi);
+        for (int r = 0; r < span; r += 16) {
+            const ColumnRows next = load(at + r + 16, hi);
+            if (aligned) add_rows<0, false>(v, 0, rows - r, s);
+            else add_rows<0, true>(v, lo - at - r, rows, s);
+            v = next;
+        }
+#pragma unroll
+        for (int q = 0; q < NV1; ++q) part[k][q][c] = s[q];
+    }
+    __syncthreads();
+    if (tid < NV1 * CW) {
+        const int q = tid / CW, o = tid % CW;
+        float s = 0.0f;
+#pragma unroll 8
+        for (int k = 0; k < n; ++k) s += part[k][q][o];
+        float *g = a.grad + (uint64_t)m * NPARAM;
+        if (q < IN) g[OFF_W1 + (f0 + o) * IN + q] = s;
+        else g[OFF_B1 + f0 + o] = s;
+    }
+}
+
+// Four slices' fragments, lane group e holding rows 8 e .. 8 e + 7 of each, transposed:
+// lane group g then holds slice g, its rows 8 e .. in q[e].
+__device__ __forceinline__ void slices_to_groups(bf16x8 (&q)[4])
+{
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    u32x4 v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = __builtin_bit_cast(u32x4, q[k]);
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {           // the halves of slices k and k + 2
+            const auto s = __builtin_amdgcn_permlane32_swap(v[k][d], v[k + 2][d], false, false);
+            v[k][d] = s[0];
+            v[k + 2][d] = s[1];
+        }
+#pragma unroll
+        for (int k = 0; k < 4; k += 2) {        // the quarters
+            const auto s = __builtin_amdgcn_permlane16_swap(v[k][d], v[k + 1][d], false, false);
+            v[k][d] = s[0];
+            v[k + 1][d] = s[1];
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) q[k] = __builtin_bit_cast(bf16x8, v[k]);
+}
+
+template <int KS> __global__ void __launch_bounds__(TBT, 2) k_train_wgrad(const TrainArgs a)
+{
+    constexpr int NI = KS == 8 ? 2 : KS == 4 ? 2 : 1;           // products of a wave: NI x NJ
+    constexpr int NJ = KS / NI;
+    constexpr int WC = TWAVES / KS;                             // waves of a chunk
+    constexpr int SL = KS == 8 ? 4 : 8;                         // slices in flight
+    static_assert(NI * NJ * WC == (WGM / 16) * (WGN / 16) && SL % 4 == 0, "the waves of a chunk cover the tile");
+    // the sums of the chunks, or the partial sums of the input layer
+    __shared__ __align__(16) union {
+        float red[KS][WGM * WGN];
+        float part[MAX_COLUMNS][NV1][CW];
+    } sm;
+    __shared__ float redb[KS][WGM];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4, c = lane & 15;
     const int nm = a.members, B = a.B;
     // Work-groups go to the 8 XCDs in turn.  XCD x takes layer 3 - x % 2 and the output
     // quarter x / 2 of every member, so its L2 reads a quarter of that layer's dz and its
     // activations once, instead of every operand (26.4 -> 24.1 us at 4096 rows).
     const int tiles = WG_TILES * nm, b = (int)blockIdx.x;
-    const int m = b < tiles ? b / WG_TILES : (b - tiles) / (NV1 + 1);
-    float *grad = a.grad + (uint64_t)m * NPARAM;
     if (b >= tiles) {
-        const int q = (b - tiles) % (NV1 + 1);
-        if (q < NV1) {
-            if (tid >= H) return;
-            const float *p = a.cpart + ((uint64_t)m * a.groups * NV1 + q) * H + tid;
-            float s = 0.0f;
-#pragma unroll 8
-            for (int k = 0; k < a.groups; ++k) s += p[(uint64_t)k * NV1 * H];
-            if (q < IN) grad[OFF_W1 + tid * IN + q] = s;
-            else grad[OFF_B1 + tid] = s;
+        const int m = (b - tiles) / (COLUMN_BLOCKS + 1), q = (b - tiles) % (COLUMN_BLOCKS + 1);
+        if (q < COLUMN_BLOCKS) {
+            column_sums(a, m, q * CW, sm.part);
         } else if (tid < HEAD_W) {
-            const float *p = a.hpart + (uint64_t)m * a.groups * HEAD_W + tid;
+            float *grad = a.grad + (uint64_t)m * NPARAM;
+            const int n = B / HEAD_ROWS;
+            const float *p = a.hpart + (uint64_t)m * n * HEAD_W + tid;
             float s = 0.0f;
-#pragma unroll 8
-            for (int k = 0; k < a.groups; ++k) s += p[(uint64_t)k * HEAD_W];
+#pragma unroll 32
+            for (int k = 0; k < n; ++k) s += p[(uint64_t)k * HEAD_W];
             if (tid < H) grad[OFF_W4 + tid] = s;
             else if (tid == H) grad[OFF_B4] = s;
             else if (a.loss) a.loss[m] = s / (float)B;
         }
         return;
     }
+    const int m = b / WG_TILES;
+    float *grad = a.grad + (uint64_t)m * NPARAM;
     const int x = b % 8, k8 = b % WG_TILES / 8;     // tile k8 of the 2 x 4 tiles of a quarter
     const bool l3 = x % 2 == 0;
     const int o0 = (x / 2 * 2 + k8 / 4) * WGM, i0 = k8 % 4 * WGN;
-    const uint64_t mT = (uint64_t)m * H * B;
-    const bf16_t *dz = (l3 ? a.dz3T : a.dz2T) + mT + o0 / 16 * 512 + lane * 8;
-    const bf16_t *av = (l3 ? a.a2T : a.a1T) + mT + i0 / 16 * 512 + lane * 8;
-    floatx4 acc[2][4];
+    // this wave's chunk and products: rows i = wi .. of the 2 x 4, columns j = wj ..
+    const int chunk = wave % KS, part = wave / KS;
+    const int wi = part / (4 / NJ) * NI, wj = part % (4 / NJ) * NJ;
+    const int ns = B / KS / 32;                     // slices of a chunk
+    const uint64_t mT = (uint64_t)m * H * B + (uint64_t)chunk * ns * (32 * H);
+    const bf16_t *dzc = (l3 ? a.dz3T : a.dz2T) + mT + (o0 / 16 + wi) * 512;
+    const bf16_t *dz = dzc + lane * 8;
+    const bf16_t *av = (l3 ? a.a2T : a.a1T) + mT + (i0 / 16 + wj) * 512 + lane * 8;
+    // Bias: the sum of quarter g of every tile of bias_tile rows, for column c of each of
+    // this wave's rows of products; the waves with wj = 0 of the first column tile.  A tile
+    // of 32 rows has its quarters in the lane groups already; one of 128 has a slice each.
+    const bool bias = i0 == 0 && wj == 0, wide = bias_tile(B / KS) == 128;
+    floatx4 acc[NI][NJ];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < NI; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-    float bs[2] = {0.0f, 0.0f};
-    constexpr int SL = 4;                       // slices in flight
-    const int ns = B / 32;
-    for (int s0 = wave; s0 < ns; s0 += SL * TWAVES) {
-        bf16x8 fa[SL][2], fb[SL][4];
+        for (int j = 0; j < NJ; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    float bs[NI] = {};
+    for (int s0 = 0; s0 < ns; s0 += SL) {
+        bf16x8 fa[SL][NI], fb[SL][NJ];
 #pragma unroll
         for (int k = 0; k < SL; ++k) {
-            const int s = s0 + k * TWAVES;
+            const int s = s0 + k;
             if (s < ns) {                       // wave-uniform
 #pragma unroll
-                for (int i = 0; i < 2; ++i)
+                for (int i = 0; i < NI; ++i)
                     fa[k][i] = *reinterpret_cast<const bf16x8 *>(dz + (uint64_t)s * (32 * H) + 512 * i);
 #pragma unroll
-                for (int j = 0; j < 4; ++j)
+                for (int j = 0; j < NJ; ++j)
                     fb[k][j] = *reinterpret_cast<const bf16x8 *>(av + (uint64_t)s * (32 * H) + 512 * j);
             }
         }
 #pragma unroll
         for (int k = 0; k < SL; ++k) {
-            if (s0 + k * TWAVES < ns) {
+            if (s0 + k < ns) {
 #pragma unroll
-                for (int i = 0; i < 2; ++i)
+                for (int i = 0; i < NI; ++i)
 #pragma unroll
-                    for (int j = 0; j < 4; ++j)
+                    for (int j = 0; j < NJ; ++j)
                         acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[k][i], fb[k][j], acc[i][j], 0, 0, 0);
-                if (i0 == 0) {
+            }
+        }
+        if (bias) {
 #pragma unroll
-                    for (int i = 0; i < 2; ++i)
+            for (int k = 0; k < SL; k += 4) {
+                if (s0 + k >= ns) break;
 #pragma unroll
-                        for (int j = 0; j < 8; ++j) bs[i] += (float)fa[k][i][j];
+                for (int i = 0; i < NI; ++i) {
+                    bf16x8 q[4] = {fa[k][i], fa[k + 1][i], fa[k + 2][i], fa[k + 3][i]};
+                    if (wide) slices_to_groups(q);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (s0 + k + e < ns) {
+#pragma unroll
+                            for (int j = 0; j < 8; ++j) bs[i] += (float)q[e][j];
+                        }
                 }
             }
         }
     }
-    // acc[i][j][e] is dW[o0 + 16 i + 4 g + e][i0 + 16 j + c] of this wave's rows
-    auto at = [&](int i, int j, int e) { return (16 * i + 4 * g + e) * WGN + 16 * j + c; };
-    if (i0 == 0) {
+    // acc[i][j][e] is dW[o0 + 16 (wi + i) + 4 g + e][i0 + 16 (wj + j) + c] of this chunk's rows
+    if (bias) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
+        for (int i = 0; i < NI; ++i) {
             bs[i] += __shfl_xor(bs[i], 16, 64);
             bs[i] += __shfl_xor(bs[i], 32, 64);
-            if (g == 0) redb[wave][16 * i + c] = bs[i];
+            if (g == 0) redb[chunk][16 * (wi + i) + c] = bs[i];
         }
     }
-    if (wave >= TWAVES / 2) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < NI; ++i)
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < NJ; ++j)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) red[wave - TWAVES / 2][at(i, j, e)] = acc[i][j][e];
-    }
-    __syncthreads();
-    if (wave < TWAVES / 2) {
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) red[wave][at(i, j, e)] += acc[i][j][e];
-    }
+            for (int e = 0; e < 4; ++e)
+                sm.red[chunk][(16 * (wi + i) + 4 * g + e) * WGN + 16 * (wj + j) + c] = acc[i][j][e];
     __syncthreads();
     float *gw = grad + (l3 ? OFF_W3 : OFF_W2);
 #pragma unroll
     for (int k = 0; k < WGM * WGN / TBT; ++k) {
         const int q = k * TBT + tid;
-        gw[(uint64_t)(o0 + q / WGN) * H + i0 + q % WGN] = (red[0][q] + red[1][q]) + (red[2][q] + red[3][q]);
+        float s = 0.0f;
+#pragma unroll
+        for (int kc = 0; kc < KS; ++kc) s += sm.red[kc][q];
+        gw[(uint64_t)(o0 + q / WGN) * H + i0 + q % WGN] = s;
     }
     if (i0 == 0 && tid < WGM) {
         float s = 0.0f;
 #pragma unroll
-        for (int w = 0; w < TWAVES; ++w) s += redb[w][tid];
+        for (int kc = 0; kc < KS; ++kc) s += redb[kc][tid];
         grad[(l3 ? OFF_B3 : OFF_B2) + o0 + tid] = s;
     }
 }

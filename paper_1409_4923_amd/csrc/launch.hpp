@@ -4,18 +4,25 @@
 
 #include "bmotor.h"
 #include "common.hpp"
+#include "settled.hpp"
 
 namespace bm {
 
-// Whether kernel K has dynamic LDS only (see lds_at); a property of the built code.
+// Whether kernel K has dynamic LDS only (see lds_at): a property of the built code, asked
+// once; a query that failed is repeated at the next launch, and leaves no error behind for
+// that launch to find.
 template <auto K> hipError_t dynamic_lds_only()
 {
-    static const hipError_t e = [] {
+    static Settled only;
+    bool yes = false;
+    const hipError_t e = only(yes, [](bool &y) {
         hipFuncAttributes f{};
         const hipError_t r = hipFuncGetAttributes(&f, reinterpret_cast<const void *>(K));
-        return r != hipSuccess ? r : f.sharedSizeBytes == 0 ? hipSuccess : hipErrorInvalidConfiguration;
-    }();
-    return e;
+        if (r != hipSuccess) (void)hipGetLastError();
+        y = f.sharedSizeBytes == 0;
+        return r;
+    });
+    return e != hipSuccess ? e : yes ? hipSuccess : hipErrorInvalidConfiguration;
 }
 
 struct ScanArgs;

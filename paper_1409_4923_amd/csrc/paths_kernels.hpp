@@ -442,7 +442,7 @@ template <typename R, int NOISE> __host__ __device__ constexpr uint32_t ring_byt
            (((NOISE & NZ_DICH) != 0) ? 4u << log2 : 0u);
 }
 // Slots that fit: the busy size while a work-group of `lanes` paths stays within 60 KiB.
-template <typename R, int NOISE> __host__ inline uint32_t ring_fit(uint32_t log2, uint32_t lanes)
+template <typename R, int NOISE> __host__ constexpr uint32_t ring_fit(uint32_t log2, uint32_t lanes)
 {
     return ring_bytes<R, NOISE>(log2) * lanes <= 61440u ? log2 : RING_LOG2;
 }

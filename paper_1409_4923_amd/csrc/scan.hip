@@ -12,6 +12,7 @@
 #include <string>
 #include <tuple>
 #include <unistd.h>
+#include <utility>
 #include <vector>
 
 #include "bmotor.h"
@@ -126,17 +127,43 @@ bm_tune scan_tune(uint32_t dyn, uint32_t pot, uint32_t noise, uint32_t prec)
     return t;
 }
 
-// LDS that decides which launch shapes a model takes: per lane and path 10 kicks of the
-// jump-adapted grid (6 in FP64) or 12 kicks, and 12 flips.  The rings of
-// paths_kernels.hpp need at most as much (ring_fit keeps them within 60 KiB).
-size_t queue_lds_bytes(uint32_t noise, uint32_t prec, uint32_t ppl, uint32_t block)
+// The rule that admits launch shapes: this many bytes per lane and path, of 64 KiB.  They
+// are the jump queues of a former step loop (10 kicks of the jump-adapted grid, 6 in FP64,
+// or 12 kicks; 12 flips), kept so that the shapes a model takes, and the tuning files that
+// hold them, stay the same.  The launch itself needs other sizes: rings of 8 slots
+// and the waves' digit tables fit every admitted shape (checked below), and rings of 16 are
+// taken where ring_fit finds room for them.
+static constexpr size_t admission_bytes(uint32_t noise, bool f32)
 {
-    const bool f32 = prec == BM_F32;
     size_t per = 0;
     if (noise & BM_NOISE_JUMP_GRID) per += f32 ? 160 : 192;
     else if (noise & BM_NOISE_POISSON) per += f32 ? 96 : 192;
     if (noise & BM_NOISE_DICH) per += 48;
-    return per * ppl * block;
+    return per;
+}
+
+template <typename R, int NOISE> static constexpr bool admitted_shapes_fit()
+{
+    constexpr bool f32 = sizeof(R) == 4;
+    for (uint32_t ppl = 1; ppl <= (f32 ? 2u : 1u); ++ppl)
+        for (uint32_t block = 64; block <= 512; block *= 2) {
+            if (admission_bytes(NOISE, f32) * ppl * block > 65536) continue;
+            for (uint32_t log2 = RING_LOG2; log2 <= RING_LOG2_BUSY; ++log2)
+                if (ring_bytes<R, NOISE>(ring_fit<R, NOISE>(log2, ppl * block)) * ppl * block +
+                        table_lds<R, NOISE>(block / 64) > 65536)
+                    return false;
+        }
+    return true;
+}
+template <int... NOISE> static constexpr bool all_fit(std::integer_sequence<int, NOISE...>)
+{
+    return ((admitted_shapes_fit<float, NOISE>() && admitted_shapes_fit<double, NOISE>()) && ...);
+}
+static_assert(all_fit(std::make_integer_sequence<int, 32>{}), "an admitted launch shape exceeds 64 KiB of LDS");
+
+size_t queue_lds_bytes(uint32_t noise, uint32_t prec, uint32_t ppl, uint32_t block)
+{
+    return admission_bytes(noise, prec == BM_F32) * ppl * block;
 }
 
 int check_tune(const bm_tune *t, uint32_t noise, uint32_t prec)

@@ -24,9 +24,11 @@ void forcing_table(const bm_model *m, const bm_run *r, std::vector<double> &tab)
 PointConst point_const(const bm_model *m, const bm_run *r, const void *d_tab);
 int check_device(int *dev_out);                     // a gfx950 device is current
 
-// Launch shape used when the caller passes no bm_tune: set by bm_tune_set_default
-// (or bm_scan_autotune), else the built-in shape of the model, for an ensemble of
-// n_paths (default: many).
+// Launch shapes for calls without a bm_tune: the one installed for the model (by
+// bm_tune_set_default, bm_scan_autotune or bm_tune_load), else a built-in one.
+// ensemble_tune is what ensembles run; default_tune is what bm_tune_get_default and
+// bm_tune_lookup report, which for FP32 inertial models without jumps is the shape that
+// ensembles used to run (programs may rely on the answer).
 bm_tune default_tune(uint32_t dyn, uint32_t pot, uint32_t noise, uint32_t prec);
 bm_tune ensemble_tune(uint32_t dyn, uint32_t pot, uint32_t noise, uint32_t prec);
 size_t queue_lds_bytes(uint32_t noise, uint32_t prec, uint32_t ppl, uint32_t block);

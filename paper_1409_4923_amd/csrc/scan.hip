@@ -89,7 +89,9 @@ bool f32_inertial_no_jumps(uint32_t dyn, uint32_t noise, uint32_t prec)
 }
 } // namespace
 
-// The shape bm_tune_get_default and bm_tune_lookup report.
+// The shape bm_tune_get_default and bm_tune_lookup report: for FP32 inertial models without
+// jumps still two paths per lane, though no call without a bm_tune runs it any more (see
+// ensemble_tune and scan_tune): the answers of these calls stay what they were.
 bm_tune default_tune(uint32_t dyn, uint32_t pot, uint32_t noise, uint32_t prec)
 {
     bm_tune t = builtin_tune();

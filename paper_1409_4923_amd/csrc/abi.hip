@@ -299,12 +299,11 @@ PointConst point_const(const bm_model *m, const bm_run *r, const void *d_tab)
     // 1 - phi, v_log_f32 near 1, the scale); the tolerance is about 7x / 10x that.
     const double LN2 = 0.69314718055994530942;
     k.tol1 = 4e-6f;
-    // Jump rings of 16 slots where a lane expects more than 1.6 jumps in a block of 16
-    // steps (the fastest rate of the model decides), else of 8.
+    // Sizes of the jump rings: the fastest rate of the model decides.
     double rate_dt = 0.0;
     if (m->noise & BM_NOISE_POISSON) rate_dt = std::fmax(rate_dt, m->shot_rate * h);
     if (m->noise & BM_NOISE_DICH) rate_dt = std::fmax(rate_dt, std::fmax(m->dich_mua, m->dich_mub) * h);
-    k.ring_log2 = rate_dt > 0.1 ? RING_LOG2_BUSY : RING_LOG2;
+    k.busy = rate_dt > 0.2 ? 2u : rate_dt > 0.1 ? 1u : 0u;
     if (m->noise & BM_NOISE_POISSON) {
         k.lam_dt = m->shot_rate * h;
         k.zeta = m->shot_mean;

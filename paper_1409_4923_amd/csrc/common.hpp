@@ -93,6 +93,9 @@ struct Partial {
     uint64_t n, n_bad;     // finite / non-finite counts
 };
 
+// Slots of the jump rings: 2^log2 of kicks and of flips, jg of kicks of the jump-adapted grid.
+struct RingSizes { uint32_t log2, jg; };
+
 // ---------------------------------------------------------------------------
 // Constants of one parameter point (one ensemble, or one point of a scan).
 // ---------------------------------------------------------------------------
@@ -102,7 +105,8 @@ struct PointConst {
     uint32_t point;       // point index in the random-stream counter
     uint32_t key0, key1;  // Philox key (seed)
     uint32_t n_paths;
-    uint32_t ring_log2;   // slots of the jump rings: 2^ring_log2
+    uint32_t busy;        // jump rates, see ring_sizes
+    RingSizes rings;      // filled by the launcher
     uint64_t n_steps;     // horizon (scan)
     uint64_t n_window;    // eq. (31): step index of t_i
     double dt, gamma;

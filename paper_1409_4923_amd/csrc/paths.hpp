@@ -202,10 +202,6 @@ template <int POT, typename R> __device__ __forceinline__ void fold(Path<R> &s)
 // sentinel with the step of the first jump not drawn yet.
 // ---------------------------------------------------------------------------
 
-// Slots of a ring of 2^log2 entries: 8, or 16 where a lane expects more than 1.6 jumps in
-// 16 steps (a full ring cuts the block short).
-constexpr uint32_t RING_LOG2 = 3, RING_LOG2_BUSY = 4;
-
 // A kick of the jump-adapted grid, drawn ahead: its step, the fraction of that step at
 // which it falls, its amplitude, and the Gaussian increment (times G sqrt(3 dt) or
 // G sqrt(dt)) of the piece that follows it.
@@ -213,10 +209,25 @@ template <typename R> struct alignas(4 * sizeof(R)) JGKick {
     uint32_t off;
     R th, z, u;
 };
-// Slots of its ring: 9 in FP32, the most that four groups of 256 lanes hold in a CU's
-// LDS; 6 in FP64, so that the FP64 rings of 256 lanes with the dichotomous ring still fit
-// in 64 KiB.  A step with more kicks draws the rest at the step.
-template <typename R> constexpr uint32_t jg_slots() { return sizeof(R) == 4 ? 9u : 6u; }
+
+// Slots of the rings by the model's fastest rate: busy = 0 up to 0.1 jumps per step, 1 up to
+// 0.2, 2 beyond.  A full ring cuts the block short, a larger one costs groups per CU.
+// Kicks of the fixed grid and flips: 8 slots, or 16 where a lane expects more
+// than 1.6 jumps in 16 steps.
+// Kicks of the jump-adapted grid: 6 in FP64, so that the rings of 256 lanes with flips
+// fit in 64 KiB.  In FP32 9, the most that four groups of 256 lanes hold in a CU's LDS, or 12,
+// with three groups (500001 paths, us per step with 9 and 12: 1.75 and 1.82 at 0.1 kicks per
+// step, 2.22 and 2.22 at 0.15, 3.96 and 3.60 at 0.3, 23.5 and 20.5 at 2).  With flips 9
+// beside 16 flips, three groups as well (without the digit tables of three-point increments:
+// 2.41 us at 0.15, 20.7 at 2; 12 beside 8 leave two: 2.86 and 20.5); with the tables both
+// leave two, and 12 beside 8 is the better (3.22 against 3.36 us at 0.15, 26.5 against 31.3
+// at 2).  A step with more kicks than its ring draws the rest at the step.
+template <typename R, int NOISE> constexpr RingSizes ring_sizes(uint32_t busy)
+{
+    constexpr bool JG = sizeof(R) == 4 && (NOISE & NZ_JGRID) != 0, FLIPS = (NOISE & NZ_DICH) != 0;
+    if (JG && FLIPS && (NOISE & NZ_GAUSS) != 0) return busy >= 1u ? RingSizes{3, 12} : RingSizes{3, 9};
+    return RingSizes{busy >= 1u ? 4u : 3u, sizeof(R) != 4 ? 6u : JG && !FLIPS && busy >= 2u ? 12u : 9u};
+}
 
 // A queued kick: its step and amplitude (FP64: 12 bytes, so that LDS does not limit the
 // groups of a CU).

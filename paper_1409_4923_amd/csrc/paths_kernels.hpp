@@ -451,17 +451,18 @@ template <typename R> __device__ __forceinline__ Pair<R> digit_pair(uint32_t tab
     return lds_at<Pair<R>>(off);
 }
 
-// LDS bytes of the rings per lane and path, with rings of 2^log2 slots.
-template <typename R, int NOISE> __host__ __device__ constexpr uint32_t ring_bytes(uint32_t log2)
+// LDS bytes of the rings per lane and path.
+template <typename R, int NOISE> __host__ __device__ constexpr uint32_t ring_bytes(RingSizes n)
 {
-    return (queued_kicks<NOISE>() ? (uint32_t)sizeof(KickEntry<R>) << log2 : 0u) +
-           (((NOISE & NZ_JGRID) != 0) ? jg_slots<R>() * (uint32_t)sizeof(JGKick<R>) : 0u) +
-           (((NOISE & NZ_DICH) != 0) ? 4u << log2 : 0u);
+    return (queued_kicks<NOISE>() ? (uint32_t)sizeof(KickEntry<R>) << n.log2 : 0u) +
+           (((NOISE & NZ_JGRID) != 0) ? n.jg * (uint32_t)sizeof(JGKick<R>) : 0u) +
+           (((NOISE & NZ_DICH) != 0) ? 4u << n.log2 : 0u);
 }
-// Slots that fit: the busy size while a work-group of `lanes` paths stays within 60 KiB.
-template <typename R, int NOISE> __host__ constexpr uint32_t ring_fit(uint32_t log2, uint32_t lanes)
+// Sizes that fit: the busy ones while a work-group of `lanes` paths stays within 60 KiB.
+template <typename R, int NOISE> __host__ constexpr RingSizes ring_fit(uint32_t busy, uint32_t lanes)
 {
-    return ring_bytes<R, NOISE>(log2) * lanes <= 61440u ? log2 : RING_LOG2;
+    const RingSizes n = ring_sizes<R, NOISE>(busy);
+    return ring_bytes<R, NOISE>(n) * lanes <= 61440u ? n : ring_sizes<R, NOISE>(0);
 }
 
 // The smallest of the lanes' values, at most `most`; one lane's value, the same in every
@@ -495,9 +496,9 @@ __device__ __forceinline__ void advance_range(const PointConst &a, const uint32_
 {
     constexpr bool KICKS = queued_kicks<NOISE>(), JG = (NOISE & NZ_JGRID) != 0, FLIPS = (NOISE & NZ_DICH) != 0;
     constexpr bool JUMPS = KICKS || JG || FLIPS;
-    const uint32_t slots = 1u << a.ring_log2;
+    const uint32_t slots = 1u << a.rings.log2;
     Ring kr{0u, qs * (uint32_t)sizeof(KickEntry<R>), slots * qs * (uint32_t)sizeof(KickEntry<R>)};
-    Ring gr{0u, qs * (uint32_t)sizeof(JGKick<R>), jg_slots<R>() * qs * (uint32_t)sizeof(JGKick<R>)};
+    Ring gr{0u, qs * (uint32_t)sizeof(JGKick<R>), a.rings.jg * qs * (uint32_t)sizeof(JGKick<R>)};
     Ring fr{KICKS ? kr.total : (JG ? gr.total : 0u), qs * 4u, slots * qs * 4u};
     const uint32_t dtab = fr.base + (FLIPS ? fr.total : 0u) +
                           digit_bytes<R, NOISE>() * (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -546,7 +547,7 @@ __device__ __forceinline__ void advance_range(const PointConst &a, const uint32_
     // 2.39 ms).  Poisson kicks come often enough (0.016 per step: some lane of the wave
     // kicks in 98% of all four steps) that looking ahead only costs (2.81 -> 2.83 ms).
     constexpr bool AHEAD = FLIPS && (NOISE & NZ_POISSON) == 0;
-    const bool busy = a.ring_log2 > RING_LOG2;    // some lane flips in most fours
+    const bool busy = a.rings.log2 > 3u;          // some lane flips in most fours
 
     while (n < n1) {
         const uint64_t stop = n < a.n_window && a.n_window < n1 ? a.n_window : n1;

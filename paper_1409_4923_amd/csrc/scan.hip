@@ -132,9 +132,9 @@ bm_tune scan_tune(uint32_t dyn, uint32_t pot, uint32_t noise, uint32_t prec)
 // The rule that admits launch shapes: this many bytes per lane and path, of 64 KiB.  They
 // are the jump queues of a former step loop (10 kicks of the jump-adapted grid, 6 in FP64,
 // or 12 kicks; 12 flips), kept so that the shapes a model takes, and the tuning files that
-// hold them, stay the same.  The launch itself needs other sizes: rings of 8 slots
-// and the waves' digit tables fit every admitted shape (checked below), and rings of 16 are
-// taken where ring_fit finds room for them.
+// hold them, stay the same.  The launch itself needs other sizes: the smaller rings
+// and the waves' digit tables fit every admitted shape (checked below), and the larger ones
+// are taken where ring_fit finds room for them.
 static constexpr size_t admission_bytes(uint32_t noise, bool f32)
 {
     size_t per = 0;
@@ -150,8 +150,8 @@ template <typename R, int NOISE> static constexpr bool admitted_shapes_fit()
     for (uint32_t ppl = 1; ppl <= (f32 ? 2u : 1u); ++ppl)
         for (uint32_t block = 64; block <= 512; block *= 2) {
             if (admission_bytes(NOISE, f32) * ppl * block > 65536) continue;
-            for (uint32_t log2 = RING_LOG2; log2 <= RING_LOG2_BUSY; ++log2)
-                if (ring_bytes<R, NOISE>(ring_fit<R, NOISE>(log2, ppl * block)) * ppl * block +
+            for (uint32_t busy = 0; busy <= 2; ++busy)
+                if (ring_bytes<R, NOISE>(ring_fit<R, NOISE>(busy, ppl * block)) * ppl * block +
                         table_lds<R, NOISE>(block / 64) > 65536)
                     return false;
         }
@@ -614,13 +614,13 @@ static int plan_create(const bm_model *models, const bm_run *runs, size_t n, con
     uint64_t chunk_off = 0;
     const uint32_t per_item = 64u * t.paths_per_lane;
     uint64_t n_items = 0;
-    uint32_t ring_log2 = RING_LOG2;
+    uint32_t busy = 0;
     uint32_t last = 0;
     uint64_t last_phase = 0;
     bool sorted = true;                      // already longest horizon first
     for (size_t i = 0; i < n; ++i) {
         pcs[i] = point_const(&models[i], &runs[i], ws + tab_off);
-        ring_log2 = std::max(ring_log2, pcs[i].ring_log2);
+        busy = std::max(busy, pcs[i].busy);
         tab_off += table_entries(&runs[i]) * rs;
         red[i].off = chunk_off;
         red[i].n_chunks = (runs[i].n_paths + 63) / 64;
@@ -670,7 +670,7 @@ static int plan_create(const bm_model *models, const bm_run *runs, size_t n, con
     a.part = (Partial *)(ws + L.part);
     a.counter = (uint32_t *)(ws + L.counter);
     a.n_items = (uint32_t)n_items;
-    a.ring_log2 = ring_log2;
+    a.busy = busy;
 
     bm_scan_plan *p = new (std::nothrow) bm_scan_plan();
     if (!p) return fail(BM_ERR_INVALID_ARG, "out of host memory");

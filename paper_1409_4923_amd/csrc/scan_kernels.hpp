@@ -33,7 +33,8 @@ struct ScanArgs {
     Partial *part;
     uint32_t *counter;
     uint32_t n_items;
-    uint32_t ring_log2;   // slots of the jump rings, the same for all points
+    uint32_t busy;        // the points' fastest jump rate
+    RingSizes rings;      // of all points
 };
 
 template <typename R, int DYN, int POT, int NOISE, int PPL>
@@ -50,7 +51,7 @@ __global__ void __launch_bounds__(512) k_scan(const ScanArgs a)
         if (it >= a.n_items) break;                      // every wave exits here
         const ScanItem item = a.items[it];
         PointConst P = a.points[item.point];
-        P.ring_log2 = a.ring_log2;
+        P.rings = a.rings;
         const uint32_t base = item.chunk * 64u * PPL + lane;
         uint32_t path[PPL];
         bool valid[PPL];

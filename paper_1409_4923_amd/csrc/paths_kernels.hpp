@@ -465,15 +465,23 @@ template <typename R, int NOISE> __host__ constexpr RingSizes ring_fit(uint32_t 
     return ring_bytes<R, NOISE>(n) * lanes <= 61440u ? n : ring_sizes<R, NOISE>(0);
 }
 
-// The smallest of the lanes' values, at most `most`; one lane's value, the same in every
-// lane: kept scalar, so that step numbers and forcing-table reads stay wave-uniform.
-__device__ __forceinline__ uint32_t wave_min(uint32_t v, uint32_t most)
+// The smallest of the lanes' values, the same in every lane: kept scalar, so that step
+// numbers and forcing-table reads stay wave-uniform.
+__device__ __forceinline__ uint32_t wave_min(uint32_t v)
 {
-    for (;;) {
-        const uint64_t b = __ballot(v < most);
-        if (b == 0) return most;
-        most = __builtin_amdgcn_readfirstlane((uint32_t)__shfl(v, __ffsll((long long)b) - 1));
-    }
+    auto take = [&](auto ctrl, auto rows) {      // lanes without a source keep their value
+        const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, decltype(ctrl)::value,
+                                                                 decltype(rows)::value, 0xF, false);
+        v = o < v ? o : v;
+    };
+    using std::integral_constant;
+    take(integral_constant<int, 0x111>{}, integral_constant<int, 0xF>{});      // row_shr 1, 2, 4, 8
+    take(integral_constant<int, 0x112>{}, integral_constant<int, 0xF>{});
+    take(integral_constant<int, 0x114>{}, integral_constant<int, 0xF>{});
+    take(integral_constant<int, 0x118>{}, integral_constant<int, 0xF>{});
+    take(integral_constant<int, 0x142>{}, integral_constant<int, 0xA>{});      // last lanes of rows 0, 2
+    take(integral_constant<int, 0x143>{}, integral_constant<int, 0xC>{});      // of the lower half
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 
 // ---------------------------------------------------------------------------
@@ -548,6 +556,7 @@ __device__ __forceinline__ void advance_range(const PointConst &a, const uint32_
     // kicks in 98% of all four steps) that looking ahead only costs (2.81 -> 2.83 ms).
     constexpr bool AHEAD = FLIPS && (NOISE & NZ_POISSON) == 0;
     const bool busy = a.rings.log2 > 3u;          // some lane flips in most fours
+    uint32_t safe = (uint32_t)n0;                 // the jumps before this step are queued, in every lane
 
     while (n < n1) {
         const uint64_t stop = n < a.n_window && a.n_window < n1 ? a.n_window : n1;
@@ -568,7 +577,7 @@ __device__ __forceinline__ void advance_range(const PointConst &a, const uint32_
                 }
                 return c;
             };
-            if (__builtin_amdgcn_ballot_w64(cover() < run) != 0) {
+            if (safe - n32 < run) {
                 // steps left in the call; at most 2^30, so that the jump after the last one
                 // drawn (a countdown is below 2^31) lies less than 2^32 steps ahead
                 const uint32_t left = n1 - n < 0x40000000u ? (uint32_t)(n1 - n) : 0x40000000u;
@@ -584,11 +593,13 @@ __device__ __forceinline__ void advance_range(const PointConst &a, const uint32_
                 } while (__builtin_amdgcn_ballot_w64(more) != 0);
                 // full rings cut the block short (on the fixed grid not to nothing: the
                 // queued jumps of one lane are at different steps)
-                run = wave_min(cover(), run);
+                const uint32_t c = wave_min(cover());
+                run = c < run ? c : run;
                 if constexpr (JG) {
                     single = run == 0u;
                     run = single ? 1u : run;
                 }
+                safe = n32 + (c > run ? c : run);
 #pragma unroll
                 for (int j = 0; j < PPL; ++j) {   // sentinels, and the current entries again
                     if constexpr (KICKS) {
@@ -656,7 +667,13 @@ __device__ __forceinline__ void advance_range(const PointConst &a, const uint32_
                 for (uint32_t t = 0; t < run; ++t) one_step(std::false_type{}, q);
             }
         } else {
-            do {                                      // without jumps one check covers many blocks
+            // whole blocks to the next refill or stop, without another look
+            uint32_t blocks = 0;
+            if constexpr (JUMPS) {
+                blocks = (stop - n < 0x40000000u ? (uint32_t)(stop - n) : 0x40000000u) >> 4;
+                blocks = (safe - n32) >> 4 < blocks ? (safe - n32) >> 4 : blocks;
+            }
+            do {
                 uint32_t off = (uint32_t)n;
                 U4 q[PPL];
 #pragma unroll
@@ -729,7 +746,7 @@ __device__ __forceinline__ void advance_range(const PointConst &a, const uint32_
                 if constexpr ((NOISE & NZ_NORMAL) != 0) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int j = 0; j < PPL; ++j) fold<POT, R>(s[j]);   // x mod L at the block end
-            } while (!JUMPS && n + 16u <= stop);
+            } while (JUMPS ? --blocks != 0u : n + 16u <= stop);
         }
         if (n == a.n_window) snap();
     }

@@ -727,12 +727,17 @@ extern "C" int bm_mlp_backward(uint32_t n_members, const float *d_params, const 
     a.grad = d_grad;
     a.loss = d_loss;
     hipLaunchKernelGGL(k_train_rows, dim3((uint32_t)a.groups, n_members), dim3(TBT), 0, s, a);
-    const dim3 grid(WG_BLOCKS * n_members);
+    auto wgrad = [&](auto kernel, int wgm) {
+        hipLaunchKernelGGL(kernel, dim3(wg_blocks(wgm) * n_members), dim3(TBT), 0, s, a);
+    };
     switch (wgrad_split((int)batch)) {
-    case 1: hipLaunchKernelGGL(k_train_wgrad<1>, grid, dim3(TBT), 0, s, a); break;
-    case 2: hipLaunchKernelGGL(k_train_wgrad<2>, grid, dim3(TBT), 0, s, a); break;
-    case 4: hipLaunchKernelGGL(k_train_wgrad<4>, grid, dim3(TBT), 0, s, a); break;
-    default: hipLaunchKernelGGL(k_train_wgrad<8>, grid, dim3(TBT), 0, s, a); break;
+    case 1: wgrad(&k_train_wgrad<1, 32>, 32); break;
+    case 2:
+        if (n_members >= WGRAD_TALL) wgrad(&k_train_wgrad<2, 64>, 64);
+        else wgrad(&k_train_wgrad<2, 32>, 32);
+        break;
+    case 4: wgrad(&k_train_wgrad<4, 32>, 32); break;
+    default: wgrad(&k_train_wgrad<8, 32>, 32); break;
     }
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? ok() : hip_fail(e, "bm_mlp_backward");

@@ -399,21 +399,28 @@ __global__ void __launch_bounds__(TBT, 2) k_train_rows(const TrainArgs a)
 }
 
 // Weight gradients dW[o][i] = sum_r dz[r][o] a[r][i] of the 256 x 256 layers from the
-// fragments of k_train_rows, KS = wgrad_split(B): grid (64 + COLUMN_BLOCKS + 1) members; a
-// group of the first 64 members forms a 32 x 64 tile.  Its eight waves share the KS chunks
-// of rows, 8 / KS waves to a chunk with KS of the tile's eight 16 x 16 products each, so
-// that a product is one accumulation over its chunk and all waves work at any batch; up to
-// SL slices of 32 rows have their loads in flight.  The chunks are added in order through
-// LDS, which needs no partials in memory.  The bias gradients are row sums of dz in the
-// groups of the first column tile.  The last (COLUMN_BLOCKS + 1) members blocks form the
-// gradients of the input layer and add the records of the output layer.
-// 9.8 us at 1024 rows and 24.9 us at 4096; slices dealt to the waves in turn (a quarter
-// fewer loads at KS = 4, but sums in another order) took 10.4 and 24.0 us.
-constexpr int WG_TILES = 64;
+// fragments of k_train_rows, KS = wgrad_split(B): grid wg_blocks(WGM) members; a group of
+// the first wg_tiles(WGM) members forms a WGM x 64 tile.  Its eight waves share the KS chunks
+// of rows, 8 / KS waves to a chunk with as many 16 x 16 products of the tile each, so that a
+// product is one accumulation over its chunk and all waves work at any batch; up to SL slices
+// of 32 rows have their loads in flight.  The chunks are added in order through LDS, which
+// needs no partials in memory.  The bias gradients are row sums of dz in the groups of the
+// first column tile.  The last (COLUMN_BLOCKS + 1) members blocks form the gradients of the
+// input layer and add the records of the output layer.
+// 5 members: 9.8 us at 1024 rows and 24.9 us at 4096; slices dealt to the waves in turn (a
+// quarter fewer loads at KS = 4, but sums in another order) took 10.4 and 24.0 us.
+// At KS = 2 (a batch that is an odd multiple of 64, from 512 on) four waves share a chunk,
+// with two products of a 32 x 64 tile each for three fragments, and the chunks are long: the
+// loads count.  Where the tiles of 32 rows are more than the 256 CUs take at once, from five
+// members on, tiles of 64 rows (four products for four fragments, half the groups) and the
+// next slices fetched ahead take less: 5 members x 4032 rows 89 us a gradient against 99 (90
+// with the slices in turn), but 3 members 68 against 62.
 constexpr int CW = 16;                          // columns of the input layer per block
 constexpr int COLUMN_BLOCKS = H / CW;
-constexpr int WG_BLOCKS = WG_TILES + COLUMN_BLOCKS + 1;   // per member
-constexpr int WGM = 32, WGN = 64;
+constexpr int WGN = 64;
+constexpr int wg_tiles(int wgm) { return 2 * (H / wgm) * (H / WGN); }                  // per member
+constexpr int wg_blocks(int wgm) { return wg_tiles(wgm) + COLUMN_BLOCKS + 1; }
+constexpr uint32_t WGRAD_TALL = 256 / wg_tiles(32) + 1;   // members whose 32-row tiles exceed the CUs
 
 // The value of lane I of this lane's row of 16.
 template <int I> __device__ __forceinline__ float row_lane(float v)
@@ -523,12 +530,15 @@ __device__ __forceinline__ void slices_to_groups(bf16x8 (&q)[4])
     for (int k = 0; k < 4; ++k) q[k] = __builtin_bit_cast(bf16x8, v[k]);
 }
 
-template <int KS> __global__ void __launch_bounds__(TBT, 2) k_train_wgrad(const TrainArgs a)
+template <int KS, int WGM> __global__ void __launch_bounds__(TBT, 2) k_train_wgrad(const TrainArgs a)
 {
-    constexpr int NI = KS == 8 ? 2 : KS == 4 ? 2 : 1;           // products of a wave: NI x NJ
-    constexpr int NJ = KS / NI;
+    constexpr int WG_TILES = wg_tiles(WGM);
     constexpr int WC = TWAVES / KS;                             // waves of a chunk
-    constexpr int SL = KS == 8 ? 4 : 8;                         // slices in flight
+    constexpr int PROD = (WGM / 16) * (WGN / 16) / WC;          // products of a wave: NI x NJ
+    constexpr int NI = PROD >= 4 ? 2 : 1;
+    constexpr int NJ = PROD / NI;
+    constexpr bool AHEAD = WGM > 32;                            // the next slices are fetched ahead
+    constexpr int SL = AHEAD || KS == 8 ? 4 : 8;                // slices in flight
     static_assert(NI * NJ * WC == (WGM / 16) * (WGN / 16) && SL % 4 == 0, "the waves of a chunk cover the tile");
     // the sums of the chunks, or the partial sums of the input layer
     __shared__ __align__(16) union {
@@ -561,10 +571,10 @@ template <int KS> __global__ void __launch_bounds__(TBT, 2) k_train_wgrad(const 
     }
     const int m = b / WG_TILES;
     float *grad = a.grad + (uint64_t)m * NPARAM;
-    const int x = b % 8, k8 = b % WG_TILES / 8;     // tile k8 of the 2 x 4 tiles of a quarter
+    const int x = b % 8, k8 = b % WG_TILES / 8;     // tile k8 of the quarter's, four to a row
     const bool l3 = x % 2 == 0;
-    const int o0 = (x / 2 * 2 + k8 / 4) * WGM, i0 = k8 % 4 * WGN;
-    // this wave's chunk and products: rows i = wi .. of the 2 x 4, columns j = wj ..
+    const int o0 = x / 2 * (H / 4) + k8 / 4 * WGM, i0 = k8 % 4 * WGN;
+    // this wave's chunk and products: rows i = wi .. of the tile's, columns j = wj ..
     const int chunk = wave % KS, part = wave / KS;
     const int wi = part / (4 / NJ) * NI, wj = part % (4 / NJ) * NJ;
     const int ns = B / KS / 32;                     // slices of a chunk
@@ -582,44 +592,98 @@ template <int KS> __global__ void __launch_bounds__(TBT, 2) k_train_wgrad(const 
 #pragma unroll
         for (int j = 0; j < NJ; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
     float bs[NI] = {};
-    for (int s0 = 0; s0 < ns; s0 += SL) {
-        bf16x8 fa[SL][NI], fb[SL][NJ];
+    if constexpr (AHEAD) {
+        struct Slices {
+            bf16x8 a[SL][NI], b[SL][NJ];
+        } f0, f1;
+        auto load = [&](int s0, Slices &f) {
 #pragma unroll
-        for (int k = 0; k < SL; ++k) {
-            const int s = s0 + k;
-            if (s < ns) {                       // wave-uniform
+            for (int k = 0; k < SL; ++k) {
+                const int s = s0 + k;
+                if (s < ns) {                   // wave-uniform
 #pragma unroll
-                for (int i = 0; i < NI; ++i)
-                    fa[k][i] = *reinterpret_cast<const bf16x8 *>(dz + (uint64_t)s * (32 * H) + 512 * i);
-#pragma unroll
-                for (int j = 0; j < NJ; ++j)
-                    fb[k][j] = *reinterpret_cast<const bf16x8 *>(av + (uint64_t)s * (32 * H) + 512 * j);
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < SL; ++k) {
-            if (s0 + k < ns) {
-#pragma unroll
-                for (int i = 0; i < NI; ++i)
+                    for (int i = 0; i < NI; ++i)
+                        f.a[k][i] = *reinterpret_cast<const bf16x8 *>(dz + (uint64_t)s * (32 * H) + 512 * i);
 #pragma unroll
                     for (int j = 0; j < NJ; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[k][i], fb[k][j], acc[i][j], 0, 0, 0);
+                        f.b[k][j] = *reinterpret_cast<const bf16x8 *>(av + (uint64_t)s * (32 * H) + 512 * j);
+                }
             }
+        };
+        auto add = [&](int s0, const Slices &f) {
+#pragma unroll
+            for (int k = 0; k < SL; ++k)
+                if (s0 + k < ns) {
+#pragma unroll
+                    for (int i = 0; i < NI; ++i)
+#pragma unroll
+                        for (int j = 0; j < NJ; ++j)
+                            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.a[k][i], f.b[k][j], acc[i][j], 0, 0, 0);
+                }
+            if (bias) {
+#pragma unroll
+                for (int k = 0; k < SL; k += 4) {
+                    if (s0 + k >= ns) break;
+#pragma unroll
+                    for (int i = 0; i < NI; ++i) {
+                        bf16x8 q[4] = {f.a[k][i], f.a[k + 1][i], f.a[k + 2][i], f.a[k + 3][i]};
+                        if (wide) slices_to_groups(q);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            if (s0 + k + e < ns) {
+#pragma unroll
+                                for (int j = 0; j < 8; ++j) bs[i] += (float)q[e][j];
+                            }
+                    }
+                }
+            }
+        };
+        load(0, f0);
+        for (int s0 = 0; s0 < ns; s0 += 2 * SL) {
+            load(s0 + SL, f1);
+            add(s0, f0);
+            load(s0 + 2 * SL, f0);
+            add(s0 + SL, f1);
         }
-        if (bias) {
+    } else {
+        for (int s0 = 0; s0 < ns; s0 += SL) {
+            bf16x8 fa[SL][NI], fb[SL][NJ];
 #pragma unroll
-            for (int k = 0; k < SL; k += 4) {
-                if (s0 + k >= ns) break;
+            for (int k = 0; k < SL; ++k) {
+                const int s = s0 + k;
+                if (s < ns) {                   // wave-uniform
 #pragma unroll
-                for (int i = 0; i < NI; ++i) {
-                    bf16x8 q[4] = {fa[k][i], fa[k + 1][i], fa[k + 2][i], fa[k + 3][i]};
-                    if (wide) slices_to_groups(q);
+                    for (int i = 0; i < NI; ++i)
+                        fa[k][i] = *reinterpret_cast<const bf16x8 *>(dz + (uint64_t)s * (32 * H) + 512 * i);
 #pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        if (s0 + k + e < ns) {
+                    for (int j = 0; j < NJ; ++j)
+                        fb[k][j] = *reinterpret_cast<const bf16x8 *>(av + (uint64_t)s * (32 * H) + 512 * j);
+                }
+            }
 #pragma unroll
-                            for (int j = 0; j < 8; ++j) bs[i] += (float)q[e][j];
-                        }
+            for (int k = 0; k < SL; ++k)
+                if (s0 + k < ns) {
+#pragma unroll
+                    for (int i = 0; i < NI; ++i)
+#pragma unroll
+                        for (int j = 0; j < NJ; ++j)
+                            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[k][i], fb[k][j], acc[i][j], 0, 0, 0);
+                }
+            if (bias) {
+#pragma unroll
+                for (int k = 0; k < SL; k += 4) {
+                    if (s0 + k >= ns) break;
+#pragma unroll
+                    for (int i = 0; i < NI; ++i) {
+                        bf16x8 q[4] = {fa[k][i], fa[k + 1][i], fa[k + 2][i], fa[k + 3][i]};
+                        if (wide) slices_to_groups(q);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            if (s0 + k + e < ns) {
+#pragma unroll
+                                for (int j = 0; j < 8; ++j) bs[i] += (float)q[e][j];
+                            }
+                    }
                 }
             }
         }

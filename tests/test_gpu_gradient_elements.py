@@ -65,7 +65,7 @@ def test_the_bound_sees_one_element(batch):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("members,batch", [(1, 64), (16, 128), (3, 512), (2, 1088), (5, 1024), (2, 2752), (2, 4096)])
+@pytest.mark.parametrize("members,batch", [(1, 64), (16, 128), (3, 512), (2, 1088), (5, 1024), (2, 2752), (5, 2752), (2, 4096)])
 def test_every_element_of_the_gradients(members, batch):
     import torch
     p = W.mlp_params(members, seed=43)

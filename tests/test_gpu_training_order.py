@@ -47,13 +47,17 @@ LAYER_BY_LAYER = {
     (3, 1088): "193a748beb6fef6ce6e70d5be6a2bf04",
     (2, 2752): "ab614794f50ed7ee86332fb3fa54d480",
     (5, 4096): "a26d40d9c8b9af964b76753c2f2e0b21",
+    (5, 576): "0c1899d92aff5473f0b30a2b37040fe3",
+    (5, 4032): "0b7dd51cf76f99c67f8c6e53836f4133",
+    (6, 2112): "d32f39f25a4b3b190808b3887a082e71",
 }
 
 
 @pytest.mark.parametrize("members,batch", sorted(LAYER_BY_LAYER))
 def test_training_run_repeats(members, batch):
-    """One and several chunks of rows, of 128-row tiles and not, partial sums of the input
-    layer that begin inside eight rows; five steps, every output."""
+    """One and several chunks of rows, of 128-row tiles and not, in weight tiles of 32 rows and
+    of 64, partial sums of the input layer that begin inside eight rows; five steps, every
+    output."""
     say("training run", members, batch)
     assert training_digest(B, members, batch) == LAYER_BY_LAYER[members, batch]
 

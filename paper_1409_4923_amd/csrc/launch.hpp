@@ -44,7 +44,10 @@ BM_DECLARE_LAUNCHERS(f64_in)
 
 // per-path velocity + wave partials, and the state export (depend on precision and L only)
 // out: also reduce to it, in the same launch (n_paths <= REDUCE_SMALL), or null
-constexpr uint32_t REDUCE_SMALL = 2048;
+// REDUCE_SMALL: one work-group of 1024 lanes takes the paths in passes, so the launch saved is
+// lost again from a second pass on (one launch against two: 4.7 and 7.3 us at 64 paths, 6.8
+// and 6.8 at 1024, 8.0 and 7.2 at 1536, 9.3 and 7.2 at 2048).
+constexpr uint32_t REDUCE_SMALL = 1024;
 hipError_t launch_velocity_f32(int pot, const KArgs &a, bm_stats *out, hipStream_t s);
 hipError_t launch_velocity_f64(int pot, const KArgs &a, bm_stats *out, hipStream_t s);
 hipError_t launch_density_f32(int pot, const KArgs &a, uint32_t n_bins, unsigned long long *hist, hipStream_t s);

@@ -883,7 +883,7 @@ __global__ void __launch_bounds__(256) k_velocity(const KArgs a)
 
 // The same and the reduction of the partials in one launch of 1024 lanes, for ensembles
 // where the second launch costs more than the parallelism of the first gives: at most
-// REDUCE_SMALL paths, two chunks of 64 per wave.
+// REDUCE_SMALL paths, one pass.
 template <typename R, int POT>
 __global__ void __launch_bounds__(1024) k_velocity_reduce(const KArgs a, bm_stats *out)
 {

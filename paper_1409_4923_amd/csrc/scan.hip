@@ -649,7 +649,8 @@ static int plan_create(const bm_model *models, const bm_run *runs, size_t n, con
 
     hipStream_t s = (hipStream_t)stream;
     he = hipMemcpyAsync(d_ws, img.data(), upload, hipMemcpyHostToDevice, s);
-    if (he == hipSuccess) {
+    const bool copying = he == hipSuccess;
+    if (copying) {
         const PointConst *dp = (const PointConst *)(ws + L.points);
         const PointFill *df = (const PointFill *)(ws + L.fill);
         const double *dph = (const double *)(ws + L.phase);
@@ -659,7 +660,10 @@ static int plan_create(const bm_model *models, const bm_run *runs, size_t n, con
             hipLaunchKernelGGL(k_scan_fill<double>, dim3((uint32_t)n), dim3(256), 0, s, dp, df, dph, (ScanItem *)(ws + L.items));
         he = hipGetLastError();
     }
-    if (he == hipSuccess) he = hipStreamSynchronize(s);      // img is released on return
+    if (copying) {                       // img is released on return, whatever else failed
+        const hipError_t done = hipStreamSynchronize(s);
+        if (he == hipSuccess) he = done;
+    }
     if (he != hipSuccess) return hip_fail(he, "scan upload");
 
     ScanArgs a;

@@ -453,7 +453,10 @@ __global__ void __launch_bounds__(INFER_BT, 2) k_mlp_infer(const float *x, uint6
 // ---------------------------------------------------------------------------
 constexpr int SWAVES = 8, SBT = 64 * SWAVES;
 constexpr int SRT = 2, SROWS = 16 * SRT;
-constexpr int INFER_PASSES = 3;        // most tiles of a group; beyond, k_mlp_infer is faster
+// Most tiles of a group; beyond, k_mlp_infer is faster (5 members: 10.2 against 20.4 us with
+// one tile per group, 14.0 and 20.3 with two, 18.0 and 20.3 with three, 22.0 and 20.6 with
+// four; 1 and 16 members the same within 2 us).
+constexpr int INFER_PASSES = 3;
 constexpr int SLD = H + 8;             // LDS row (bf16): 4 banks further per row
 static_assert(SWAVES * 32 == H, "wave w owns k-step w of the next layer");
 
@@ -767,8 +770,9 @@ extern "C" int bm_mlp_adam_step(uint32_t n_members, float *d_params, const float
 
 // Most work-groups of 256 rows whose counts every compacting group adds up for itself:
 // the sums are nblk / 512 loads per thread and group, side by side, where the scan is one
-// group's serial work and a launch (9 us at 10^6 rows); beyond, the squared work overtakes
-// it.
+// group's serial work and a launch, but their work grows with the square.  Sums against scan
+// and compaction: 4.4 and 8.9 us at 1000 groups, 6.4 and 13.7 at 4000, 12.4 and 23.4 at 8192,
+// 29 and 39 at 16384, 81 and 76 at 32768; 8192 keeps clear of where the lead turns.
 static constexpr uint64_t COMPACT_SUMS = 8192;
 
 // The kernels of a query: fused inference of every member into y, then mean, std,

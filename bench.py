@@ -40,10 +40,10 @@ FP64_PEAK_FLOPS = 78.6e12
 # reads 0.5 GiB for it: factor 2.0; WRITE_SIZE reads 1 GiB: factor 1.0).  Valid
 # only while the integration kernel's sources hash to KERNEL_SOURCES_SHA256.
 TRAFFIC_WORKLOAD = "inertial-poisson-f32-2^20"
-TRAFFIC_BYTES_PER_LAUNCH = ((10480.75 + 10323.0) / 2 * 2.0 + 28672.0 * 1.0) * 1024
+TRAFFIC_BYTES_PER_LAUNCH = ((10491.375 + 10326.0) / 2 * 2.0 + 28672.0 * 1.0) * 1024
 KERNEL_SOURCES = ("common.hpp", "paths.hpp", "paths_kernels.hpp", "paths_tu.inc", "paths_f32_in.hip",
                   "launch.hpp")
-KERNEL_SOURCES_SHA256 = "e99936ab2d55e0a85eb395591d5f0d22a57ac3eae5ee36abc7877f805965be56"
+KERNEL_SOURCES_SHA256 = "7b169a773687945c7cdcb435ce6a56df2c0ddb8646151e3c92adc5e03777dd82"
 
 
 def algorithmic_work(w):

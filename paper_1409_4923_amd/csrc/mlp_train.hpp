@@ -89,10 +89,12 @@ __device__ __forceinline__ bf16x8 pair8(const bf16_t *p)
 // W with the contraction (the outputs) along a lane's registers: each wave transposes
 // its own 32 columns in 32-wide slices through a private LDS tile, so no barrier.
 // 5 members x 1024 rows put one group of 8 waves on 160 of the 256 CUs; a pass over 32
-// rows takes 46k cycles whatever the batch, 31k of them where the 4 x 128 KiB of weights
-// come in (13 B per cycle and CU, the limit of the L1 misses in flight), so a pass of
-// more rows would amortise better, but needs the registers that hold z and the weights
-// of the next layer.
+// rows takes some 46k cycles whatever the batch (25 us the first, 20 us each further one),
+// 31k of them while the 4 x 128 KiB of weights come in: 17 B per cycle and CU, in pieces of
+// 16 bytes (W) and 8 (its transpose).  The same matrices in rows of 1 KiB, turned into
+// fragments through LDS, were measured on layer 2 only: 8.1k -> 4.4k cycles.  A pass of more
+// rows would amortise better, but needs the registers that hold z and the weights of the
+// next layer.
 __global__ void __launch_bounds__(TBT, 2) k_train_rows(const TrainArgs a)
 {
     __shared__ __align__(16) bf16_t sAct[2][TR * TLD];

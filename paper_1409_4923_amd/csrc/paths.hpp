@@ -194,10 +194,10 @@ template <int POT, typename R> __device__ __forceinline__ void fold(Path<R> &s)
 // with room draws along, so the draws of many blocks happen side by side whichever lane
 // asked for them.  (Windows of a fixed number of steps, whose draws took as many turns as
 // the lane with the most jumps needed, took 1.6 times the turns at 0.016 kicks per step.)
-// Windows -> rings, 4000 steps: 500001 paths on the jump-adapted grid 3.60 -> 3.36 ms,
-// 262147 FP64 paths with kicks 558 -> 533 us per 800 steps (rings of 24 KiB per 256 lanes
-// instead of queues of 48: four groups per CU, as the registers allow, instead of three), 2^20 inertial Poisson
-// paths 2.80 -> 2.74 ms.
+// Windows -> rings: 500001 paths x 4000 steps on the jump-adapted grid 3.60 -> 3.33 ms,
+// 262147 FP64 paths with kicks x 800 steps 558 -> 524 us (rings of 24 KiB per 256 lanes
+// instead of queues of 48: four groups per CU, as the registers allow, instead of three),
+// 2^20 inertial Poisson paths x 4000 steps 2.80 -> 2.70 ms.
 // A ring holds one jump less than its slots: the slot behind the last queued jump is a
 // sentinel with the step of the first jump not drawn yet.
 // ---------------------------------------------------------------------------

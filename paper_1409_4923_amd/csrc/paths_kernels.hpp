@@ -495,9 +495,10 @@ __device__ __forceinline__ uint32_t wave_min(uint32_t v)
 // Algorithm 2 (4 words x 4 base-6 digits; the normal increments of the
 // non-simplified scheme take one call per 4 steps) and 17 loads of the
 // forcing table; x is folded after every step whose index is a multiple of 16.
-// Before a block the rings are filled until they cover it; a lane whose full ring does
-// not cover the block cuts it short for the wave, and the steps it does cover run one by
-// one, as do the ends of a call that are no whole block.
+// Where the rings do not cover the next block they are filled until they do, and the blocks
+// they then cover run without another look; a lane whose full ring does not cover a block
+// cuts it short for the wave, and the steps it does cover run one by one, as do the ends of a
+// call that are no whole block.
 // LDS holds the rings, slot-major with the lanes' columns side by side, and behind them the
 // waves' increment tables.  A block ends at a.n_window as well, and snap() runs after that
 // step: one launch crosses the start of eq. (31)'s averaging.
